@@ -120,9 +120,9 @@ typedef struct ss_options {
 } ss_options;
 
 /* Test hook: the workgroups that publish the digit bases of the first pass
- * over the pairs publish nothing, so every tile's bounded wait for its bases
- * ends in SS_ERR_TIMEOUT (after spin_limit polls), while every kernel still
- * runs to its end.  Depth-first path.  For tests of the timeout path. */
+ * over the pairs (in the spread passes: every workgroup its counts) publish
+ * nothing, so every workgroup's bounded wait ends in SS_ERR_TIMEOUT (after
+ * spin_limit polls), while every kernel still runs to its end.  Depth-first path.  For tests of the timeout path. */
 #define SS_FAULT_NONE 0u
 #define SS_FAULT_WITHHOLD_BASES 1u
 
@@ -134,7 +134,11 @@ typedef struct ss_options {
  * 512-thread passes the bits are split evenly, ceil(ceil(log2 T) / P) per
  * pass); a Gaussian adds at most one pair per tile, so the stable tile sort
  * leaves each tile in (depth, index) order.  radix_bits, items and
- * workgroup_size apply to the passes over the pairs.  AUTO = DEPTH_FIRST,
+ * workgroup_size apply to the passes over the pairs.  At their defaults (8,
+ * 16, 512) and with frames of at most 256 tiles per axis, two spread passes
+ * take the place of duplication and of the passes over the pairs: one by
+ * tile column from the Gaussians, one by tile row from its items.  The
+ * result is the same.  AUTO = DEPTH_FIRST,
  * except that SS_FLAG_UNSORTED implies DIRECT. */
 #define SS_ALGO_AUTO 0u
 #define SS_ALGO_DEPTH_FIRST 1u
@@ -479,14 +483,14 @@ ss_status ss_preprocess(const ss_camera* camera, const ss_preprocess_desc* desc,
 typedef enum ss_kernel_kind {
   SS_KERNEL_CLEAR = 0,      /* zeroes counters and look-back state */
   SS_KERNEL_COUNT_DUP = 1,  /* direct: count, scan and duplicate fused; depth-first: count and keys */
-  SS_KERNEL_SORT_PASS = 2,  /* one digit pass of the sort over the pairs */
+  SS_KERNEL_SORT_PASS = 2,  /* one digit pass of the sort over the pairs, or the row pass */
   SS_KERNEL_RANGES = 3,     /* tile ranges */
   SS_KERNEL_COPY = 4,       /* ss_copy_bytes */
   SS_KERNEL_HIST = 5,       /* digit histograms of caller keys (ss_sort_pairs) */
   SS_KERNEL_DIGIT_BASES = 6, /* pair totals of ss_batch_count_pairs (sort passes derive
                                their digit bases from the histograms) */
   SS_KERNEL_DEPTH_PASS = 7, /* depth-first: one pass of the Gaussian depth sort */
-  SS_KERNEL_EXPAND = 8,     /* depth-first: pairs in depth order */
+  SS_KERNEL_EXPAND = 8,     /* depth-first: pairs in depth order, or the column pass */
   SS_KERNEL_RENDER = 9,     /* ss_render_frame */
   SS_KERNEL_PREPROCESS = 10, /* ss_preprocess */
   SS_KERNEL_TILE_SORT = 11, /* tile-first: each tile's run sorted by depth */

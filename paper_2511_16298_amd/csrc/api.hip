@@ -36,6 +36,7 @@ struct Options {
   uint32_t algorithm = SS_ALGO_AUTO;
   ss_timer* timer = nullptr;
   bool items_default = true;  // items_per_thread left at 0 (the frame size may choose)
+  bool shape_default = true;  // radix_bits, items_per_thread and workgroup_size at their defaults
   uint32_t spin_limit = 0;    // 0: the kernels' default
   uint32_t fault = SS_FAULT_NONE;
 };
@@ -71,6 +72,8 @@ ss_status parse_options(const ss_options* o, Options* out) {
   if (!pass_config_supported(static_cast<int>(out->radix_bits), static_cast<int>(out->items),
                              static_cast<int>(out->threads)))
     return SS_ERR_UNSUPPORTED;
+  out->shape_default =
+      out->radix_bits == kDefaultRadix && out->items == kDefaultItems && out->threads == kDefaultThreads;
   out->timer = o->timer;
   return SS_OK;
 }
@@ -291,6 +294,136 @@ DfLayout make_df_layout(uint32_t n, uint32_t n_frames, uint32_t capacity, uint64
   return L;
 }
 
+// ---------------------------------------------------------------------------
+// Spread path (spread.hip): the depth sort as above, then the column and row
+// passes.  Zeroed part: scalars, bad flag, totals, count-only scan look-back,
+// depth and span histograms, look-back words; then the plans, the frame
+// table, the Gaussian sort buffers and the column items.
+// ---------------------------------------------------------------------------
+// What the frames of a call have in common for it.
+struct SpreadShape {
+  uint32_t max_tx = 0, max_ty = 0;  // most tile columns and rows of a frame
+  uint64_t sum_tx = 0;              // tile columns of all frames
+  uint64_t col_blocks = 0;          // column-pass workgroups
+  void add(uint32_t n, uint32_t tx, uint32_t ty) {
+    max_tx = tx > max_tx ? tx : max_tx;
+    max_ty = ty > max_ty ? ty : max_ty;
+    sum_tx += tx;
+    col_blocks += (n + kColumnItems - 1) / kColumnItems;
+  }
+};
+
+// Whether a call takes the spread passes: frames of at most 256 tiles per
+// axis (a packed rectangle, and a digit of a pass, hold eight bits), the
+// passes' shape at its default, and a batch that keeps its culled
+// Gaussians (each frame's depth sort then fills its own index range).  The
+// digit passes (depthfirst.hip, onesweep.hip) serve the rest.
+bool use_spread(uint32_t n, uint32_t n_frames, const SpreadShape& sh, const Options& o) {
+  return n != 0 && o.shape_default && sh.max_tx <= 256 && sh.max_ty <= 256 &&
+         (o.algorithm == SS_ALGO_AUTO || o.algorithm == SS_ALGO_DEPTH_FIRST) &&
+         (o.flags & (SS_FLAG_UNSORTED | SS_FLAG_KEY32_LOSSY | SS_FLAG_PERSISTENT)) == 0 &&
+         (n_frames == 1 || (o.flags & SS_FLAG_DROP_CULLED) == 0);
+}
+
+struct SpreadLayout {
+  uint32_t n = 0, n_frames = 0, capacity = 0;
+  PassCfg dcfg;
+  uint32_t dblocks = 0, ck_blocks = 0, count_blocks = 0, col_blocks = 0, row_blocks = 0, row_items = 0, stride_x = 0, stride_y = 0;
+  bool seg = false;     // several frames: each one's Gaussians sorted by depth apart
+  bool carry = false;   // packed rectangles travel with the depth sort
+  size_t scalars = 0, bad = 0, totals = 0, scan_lb = 0, hist_d = 0, hist_f = 0, span = 0, lb_d = 0, lb_x = 0,
+         lb_y = 0, clear_end = 0, block_total = 0, block_frame = 0, plan = 0, item_base = 0, row_chunk = 0,
+         pair_base = 0, col_chunks = 0, row_chunks = 0, table = 0, rect = 0, key = 0, val = 0, key_alt = 0, val_alt = 0, item = 0, item_rows = 0,
+         total = 0;
+};
+
+SpreadLayout make_spread_layout(uint32_t n, uint32_t n_frames, uint32_t capacity, const SpreadShape& sh) {
+  SpreadLayout L;
+  L.n = n;
+  L.n_frames = n_frames;
+  L.capacity = capacity;
+  L.seg = n_frames > 1;
+  L.dcfg = depth_cfg(n);
+  L.dblocks = (n + L.dcfg.tile() - 1) / L.dcfg.tile() + (L.seg ? n_frames : 0u);
+  // Up to 2^23 Gaussians the depth passes absorb the rectangles' extra 8 B
+  // per Gaussian almost for free (they wait on the look-back more than on
+  // memory).  Beyond that they are bandwidth-bound, and carrying pays only
+  // where the gather it replaces is worse: a single frame's is random over
+  // all its rectangles (21.8M Gaussians: 2.95 -> 2.82 ms carried), a batch's
+  // stays inside one frame at a time, mostly in cache (64 frames, 38.8M
+  // Gaussians: 4.73 against 4.83 ms carried).
+  L.carry = n <= (1u << 23) || n_frames == 1;
+  L.ck_blocks = (n + kCountKeysTile - 1) / kCountKeysTile;
+  L.count_blocks = (n + kCountTile - 1) / kCountTile;
+  L.col_blocks = static_cast<uint32_t>(sh.col_blocks);
+  // column items number at most the pairs; every column may end in a partial
+  // workgroup, and one without items still has one
+  // 4,096 items per row-pass workgroup (1,024 threads) while its LDS lets two
+  // of them share a CU, which holds up to 80 tile rows: half the workgroups
+  // to look back over (6M-Gaussian frame 478 -> 456 us, full HD 146 -> 145,
+  // 64-frame batch 2.59 -> 2.46 ms); beyond, 2,048 (512 threads)
+  L.row_items = sh.max_ty <= 80 ? 4096 : 2048;
+  L.row_blocks = static_cast<uint32_t>((capacity + L.row_items - 1) / L.row_items + sh.sum_tx);
+  L.stride_x = (sh.max_tx + 15) / 16 * 16;
+  L.stride_y = (sh.max_ty + 15) / 16 * 16;
+  size_t off = 0;
+  const auto take = [&](size_t bytes) {
+    const size_t at = off;
+    off = align_up(off + bytes);
+    return at;
+  };
+  L.scalars = take(8 * sizeof(uint32_t));  // status, M, offsets' M and status, live
+  L.bad = take(sizeof(uint32_t));
+  L.totals = take((1 + static_cast<size_t>(n_frames)) * sizeof(uint64_t));
+  L.scan_lb = take(static_cast<size_t>(L.count_blocks) * sizeof(uint64_t));
+  L.hist_d = take(static_cast<size_t>(kHistCopies) * 4 * 256 * sizeof(uint32_t));
+  L.hist_f = take((L.seg ? static_cast<size_t>(kHistCopies) * n_frames * 4 * 256 : 0u) * sizeof(uint32_t));
+  L.span = take(static_cast<size_t>(kHistCopies) * n_frames * 2 * 256 * sizeof(uint32_t));
+  L.lb_d = take(static_cast<size_t>(4) * L.dblocks * 256 * sizeof(uint32_t));
+  L.lb_x = take(static_cast<size_t>(L.col_blocks) * L.stride_x * sizeof(uint32_t));
+  L.lb_y = take(static_cast<size_t>(L.row_blocks) * L.stride_y * sizeof(uint32_t));
+  L.clear_end = off;
+  L.block_total = take(static_cast<size_t>(L.ck_blocks) * sizeof(uint64_t));
+  L.block_frame = take(static_cast<size_t>(L.ck_blocks) * sizeof(uint32_t));
+  L.plan = take(static_cast<size_t>(n_frames) * kPlanWords * sizeof(uint32_t));
+  L.item_base = take((n_frames + 1u) * sizeof(uint32_t));
+  L.row_chunk = take((n_frames + 1u) * sizeof(uint32_t));
+  L.pair_base = take(2 * (n_frames + 1u) * sizeof(uint32_t));  // and the totals' unused workgroup counts
+  L.col_chunks = take(static_cast<size_t>(L.col_blocks) * sizeof(SpreadChunk));
+  L.row_chunks = take(static_cast<size_t>(L.row_blocks) * sizeof(SpreadChunk));
+  L.table = take(static_cast<size_t>(n_frames) * sizeof(FrameInfo));
+  L.rect = take(static_cast<size_t>(n) * (L.carry ? 2 : 1) * sizeof(uint32_t));
+  L.key = take(static_cast<size_t>(n) * sizeof(uint32_t));
+  L.val = take(static_cast<size_t>(n) * sizeof(uint32_t));
+  L.key_alt = take(static_cast<size_t>(n) * sizeof(uint32_t));
+  L.val_alt = take(static_cast<size_t>(n) * sizeof(uint32_t));
+  L.item = take(static_cast<size_t>(capacity) * sizeof(uint64_t));
+  L.item_rows = take(static_cast<size_t>(capacity) * sizeof(uint16_t));
+  L.total = off;
+  return L;
+}
+
+// The layout of a frame or batch on the path it takes: spread passes where
+// they serve the call and fit the workspace that the digit passes need, which
+// is what callers are asked for (all but frames of a few thousand Gaussians
+// on large grids, by some 10 KB); else digit passes.
+struct SortLayout {
+  bool spread = false;
+  SpreadLayout sp;
+  DfLayout df;
+};
+
+SortLayout make_sort_layout(uint32_t n, uint32_t n_frames, uint32_t capacity, uint64_t tiles, const Options& o,
+                            uint32_t max_n, uint64_t max_tiles, const SpreadShape& sh) {
+  SortLayout L;
+  L.df = make_df_layout(n, n_frames, capacity, tiles, o, max_n, max_tiles);
+  if (use_spread(n, n_frames, sh, o)) {
+    L.sp = make_spread_layout(n, n_frames, capacity, sh);
+    L.spread = L.sp.total <= L.df.total;
+  }
+  return L;
+}
+
 }  // namespace
 }  // namespace ss
 
@@ -390,6 +523,8 @@ struct PassChain {
   const uint32_t* seg_wgs;
   const uint32_t* seg_base;
   uint32_t frame_stride;
+  // the depth sort: work beside its first three passes (SideWork), or NULL
+  const SideWork* side;       // [3]
   // waits, test hook, persistent 64-bit passes (pass p's zeroed counter at
   // tickets + p; NULL: one workgroup per tile)
   uint32_t spin_limit;
@@ -431,6 +566,10 @@ ss_status run_chain(Launcher& L, uint32_t kind, const PassChain& c, hipStream_t 
       if (p == 0 && c.depth_top_out != nullptr) {
         a.depth_top_out = c.depth_top_out;
         a.hist_top = c.hist_top;
+      }
+      if (c.side != nullptr && p < 3) {
+        a.side = c.side[p];
+        a.side.side_first = c.nblocks;
       }
       a.spin_limit = c.spin_limit;
       a.fault = c.fault;
@@ -588,6 +727,23 @@ struct DfIO {
   uint32_t* frame_pair_base;    // batch only, may be NULL
 };
 
+// The index-order offsets, an optional output with a scan of its own.
+ss_status index_order_offsets(Launcher& L, const DfIO& io, uint64_t* lookback, uint32_t nblocks, uint32_t* scal,
+                              hipStream_t s) {
+  if (io.offsets == nullptr) return SS_OK;
+  CountDupArgs a{};
+  a.gaussians = io.frames->gaussians;
+  a.n = io.frames->num_gaussians;
+  a.tiles_x = io.host_table[0].tiles_x;
+  a.tiles_y = io.host_table[0].tiles_y;
+  a.offsets = io.offsets;
+  a.lookback = lookback;
+  a.num_pairs = scal + 2;
+  a.status = scal + 3;
+  a.nblocks = nblocks;
+  return L.run(SS_KERNEL_COUNT_DUP, [&] { return launch_count_dup(a, 8, false, s); });
+}
+
 // Tile-first: every tile's run (index order, after the tile passes) sorted
 // stably by depth; runs too long for LDS use the alternate pair buffer.
 ss_status sort_tile_runs(Launcher& L, const DfLayout& lay, const DfIO& io, void* ws, uint32_t* d_status,
@@ -604,20 +760,7 @@ ss_status run_depth_first(Launcher& L, const DfLayout& lay, const Options& o, co
   FrameInfo* table = at<FrameInfo>(ws, lay.table);
 
   SS_TRY(clear_and_upload(L, ws, lay.clear_end, d_status, io.host_table, lay.n_frames, table, s));
-  if (io.offsets != nullptr) {
-    // the index-order scan exists only for this optional output
-    CountDupArgs a{};
-    a.gaussians = io.frames->gaussians;
-    a.n = io.frames->num_gaussians;
-    a.tiles_x = io.host_table[0].tiles_x;
-    a.tiles_y = io.host_table[0].tiles_y;
-    a.offsets = io.offsets;
-    a.lookback = at<uint64_t>(ws, lay.scan_lb);
-    a.num_pairs = scal + 2;
-    a.status = scal + 3;
-    a.nblocks = lay.count_blocks;
-    SS_TRY(L.run(SS_KERNEL_COUNT_DUP, [&] { return launch_count_dup(a, 8, false, s); }));
-  }
+  SS_TRY(index_order_offsets(L, io, at<uint64_t>(ws, lay.scan_lb), lay.count_blocks, scal, s));
 
   uint32_t* key = at<uint32_t>(ws, lay.key);
   uint32_t* val = at<uint32_t>(ws, lay.val);
@@ -838,6 +981,132 @@ ss_status run_depth_first(Launcher& L, const DfLayout& lay, const Options& o, co
   return tile_first ? sort_tile_runs(L, lay, io, ws, d_status, s) : SS_OK;
 }
 
+// ------------------------------ spread path --------------------------------
+ss_status run_spread(Launcher& L, const SpreadLayout& lay, const SpreadShape& sh, const Options& o, const DfIO& io,
+                     void* ws, hipStream_t s) {
+  uint32_t* scal = at<uint32_t>(ws, lay.scalars);
+  uint32_t* d_status = io.status ? io.status : scal + 0;
+  uint32_t* d_num_pairs = io.num_pairs ? io.num_pairs : scal + 1;
+  FrameInfo* table = at<FrameInfo>(ws, lay.table);
+  SS_TRY(clear_and_upload(L, ws, lay.clear_end, d_status, io.host_table, lay.n_frames, table, s));
+  SS_TRY(index_order_offsets(L, io, at<uint64_t>(ws, lay.scan_lb), lay.count_blocks, scal, s));
+
+  uint32_t* key = at<uint32_t>(ws, lay.key);
+  uint32_t* val = at<uint32_t>(ws, lay.val);
+  uint32_t* key_alt = at<uint32_t>(ws, lay.key_alt);
+  uint32_t* val_alt = at<uint32_t>(ws, lay.val_alt);
+  uint32_t* rect = at<uint32_t>(ws, lay.rect);
+  uint32_t* rect_alt = lay.carry ? rect + lay.n : nullptr;
+  CountKeysArgs ck{};
+  ck.table = table;
+  ck.n_frames = lay.n_frames;
+  ck.n = lay.n;
+  ck.rect32 = rect;
+  ck.key = key;
+  ck.val = val;
+  ck.tiles_touched = io.tiles_touched;
+  ck.hist = at<uint32_t>(ws, lay.hist_d);
+  ck.frame_hist = lay.seg ? at<uint32_t>(ws, lay.hist_f) : nullptr;
+  ck.span = at<uint32_t>(ws, lay.span);
+  ck.totals = at<unsigned long long>(ws, lay.totals);
+  ck.block_total = at<unsigned long long>(ws, lay.block_total);
+  ck.block_frame = at<uint32_t>(ws, lay.block_frame);
+  ck.bad = at<uint32_t>(ws, lay.bad);
+  SS_TRY(L.run(SS_KERNEL_COUNT_DUP, [&] { return launch_count_keys(ck, s); }));
+
+  // stable depth sort, as in run_depth_first; beside its first pass the
+  // frames' plans, beside its second the totals and the status, beside its
+  // third the row pass's workgroups
+  uint32_t* live = (o.flags & SS_FLAG_DROP_CULLED) != 0 ? scal + 4 : nullptr;
+  uint32_t* pair_base = at<uint32_t>(ws, lay.pair_base);
+  SideWork side[3] = {};
+  side[0].kind = SideWork::kPlan;
+  side[0].row_items = lay.row_items;
+  side[0].n_frames = lay.n_frames;
+  side[0].table = table;
+  side[0].span = ck.span;
+  side[0].plan = at<uint32_t>(ws, lay.plan);
+  side[0].item_base = at<uint32_t>(ws, lay.item_base);
+  side[0].row_chunk = at<uint32_t>(ws, lay.row_chunk);
+  side[0].culled = (lay.seg ? ck.frame_hist : ck.hist) + 3 * 256 + 255;  // digit 255 of the top byte
+  side[0].culled_copy = (lay.seg ? lay.n_frames : 1u) * 4 * 256;
+  side[0].culled_frame = 4 * 256;
+  side[0].col_chunks = at<SpreadChunk>(ws, lay.col_chunks);
+  side[0].row_chunks = at<SpreadChunk>(ws, lay.row_chunks);
+  side[0].status = d_status;
+  side[1] = side[0];
+  side[1].kind = SideWork::kTotals;
+  side[1].totals = PairTotalsArgs{ck.totals, ck.block_total, ck.block_frame, lay.ck_blocks, ck.bad, lay.n_frames,
+                                  lay.capacity, d_num_pairs, d_status, io.frame_pairs, io.frame_pair_base};
+  side[1].totals.seg_base = pair_base;
+  side[1].totals.seg_wgs = pair_base + lay.n_frames + 1;
+  side[1].totals.seg_tile = 1;
+  side[2] = side[0];
+  side[2].kind = SideWork::kRows;
+  const void* ks[4] = {key, key_alt, key, key_alt};
+  const uint32_t* vs[4] = {val, val_alt, val, val_alt};
+  void* kd[4] = {key_alt, key, key_alt, key};
+  uint32_t* vd[4] = {val_alt, val, val_alt, val};
+  const uint32_t* ps[4] = {rect, rect_alt, rect, rect_alt};
+  uint32_t* pd[4] = {rect_alt, rect, rect_alt, rect};
+  PassChain c{};
+  c.npasses = 4;
+  c.key_bytes = 4;
+  c.radix_bits = 8;
+  c.cfg = lay.dcfg;
+  c.nblocks = lay.dblocks;
+  c.ksrc = ks;
+  c.vsrc = vs;
+  c.kdst = kd;
+  c.vdst = vd;
+  c.n_fixed = lay.n;
+  c.status = d_status;
+  c.hist = lay.seg ? ck.frame_hist : ck.hist;
+  c.hist_stride = side[0].culled_copy;
+  c.lookback = at<uint32_t>(ws, lay.lb_d);
+  c.culled = live ? side[0].culled : nullptr;
+  c.kept = live;
+  c.psrc = lay.carry ? ps : nullptr;
+  c.pdst = lay.carry ? pd : nullptr;
+  c.depth_seg = lay.seg;
+  c.table = table;
+  c.n_frames = lay.n_frames;
+  c.side = side;
+  c.spin_limit = o.spin_limit;
+  SS_TRY(run_chain(L, SS_KERNEL_DEPTH_PASS, c, s));
+
+  SpreadArgs a{};
+  a.table = table;
+  a.plan = side[0].plan;
+  a.item_base = side[0].item_base;
+  a.pair_base = pair_base;
+  a.status = d_status;
+  a.capacity = lay.capacity;
+  a.spin_limit = o.spin_limit;
+  a.fault = o.fault;
+  a.key = key;
+  a.val = val;
+  a.rect = rect;
+  a.rect_by_index = !lay.carry;
+  a.item = at<uint64_t>(ws, lay.item);
+  a.item_rows = at<uint16_t>(ws, lay.item_rows);
+  a.keys = io.keys;
+  a.values = io.values;
+  a.ranges = io.ranges;
+  a.chunks = side[0].col_chunks;
+  a.num_chunks = nullptr;
+  a.max_digits = sh.max_tx;
+  a.lb_stride = lay.stride_x;
+  a.lookback = at<uint32_t>(ws, lay.lb_x);
+  SS_TRY(L.run(SS_KERNEL_EXPAND, [&] { return launch_columns(a, lay.col_blocks, s); }));
+  a.chunks = side[0].row_chunks;
+  a.num_chunks = side[0].row_chunk + lay.n_frames;
+  a.max_digits = sh.max_ty;
+  a.lb_stride = lay.stride_y;
+  a.lookback = at<uint32_t>(ws, lay.lb_y);
+  return L.run(SS_KERNEL_SORT_PASS, [&] { return launch_rows(a, lay.row_items, lay.row_blocks, s); });
+}
+
 // ----------------------------- small frames --------------------------------
 // At most 256 tiles and 16,384 Gaussians, one frame, without the optional
 // per-Gaussian outputs: two kernels (tiny.hip).  Workspace: per-tile count
@@ -907,6 +1176,7 @@ FrameInfo frame_info(const ss_frame* f, const Geometry& g, uint32_t gauss_base, 
 struct BatchShape {
   std::vector<FrameInfo> table;
   uint64_t n = 0, tiles = 0;
+  SpreadShape spread;
   uint32_t max_n = 0;   // Gaussians of the largest frame
   uint64_t max_tiles = 0;  // tiles of the frame with the most
 };
@@ -920,6 +1190,8 @@ ss_status batch_shape(const ss_frame* frames, uint32_t n_frames, BatchShape* b) 
     Geometry g;
     SS_TRY(frame_geometry(&frames[f], &g));
     b->table[f] = frame_info(&frames[f], g, static_cast<uint32_t>(b->n), static_cast<uint32_t>(b->tiles));
+    b->table[f].col_chunk = static_cast<uint32_t>(b->spread.col_blocks);
+    b->spread.add(frames[f].num_gaussians, g.tiles_x, g.tiles_y);
     b->n += frames[f].num_gaussians;
     b->tiles += g.num_tiles;
     if (frames[f].num_gaussians > b->max_n) b->max_n = frames[f].num_gaussians;
@@ -1113,10 +1385,14 @@ ss_status ss_sort_frame(const ss_frame* frame, const ss_frame_out* out, void* wo
     return run_tiny(L, frame, g, &o2, workspace, s);
   }
   const FrameInfo fi = frame_info(frame, g, 0, 0);
-  const DfLayout lay = make_df_layout(frame->num_gaussians, 1, cap, g.num_tiles, o, frame->num_gaussians, g.num_tiles);
   DfIO io{&fi, frame, out->keys, out->values, out->tile_ranges, out->tiles_touched, out->offsets,
           out->num_pairs, out->status, nullptr, nullptr};
-  return run_depth_first(L, lay, o, io, workspace, s);
+  SpreadShape sh;
+  sh.add(frame->num_gaussians, g.tiles_x, g.tiles_y);
+  const SortLayout lay = make_sort_layout(frame->num_gaussians, 1, cap, g.num_tiles, o, frame->num_gaussians,
+                                          g.num_tiles, sh);
+  return lay.spread ? run_spread(L, lay.sp, sh, o, io, workspace, s)
+                    : run_depth_first(L, lay.df, o, io, workspace, s);
 }
 
 ss_status ss_batch_workspace_bytes(const ss_frame* frames, uint32_t n_frames, uint32_t pair_capacity,
@@ -1144,13 +1420,15 @@ ss_status ss_sort_batch(const ss_frame* frames, uint32_t n_frames, const ss_batc
   if (cap > 0 && (out->keys == nullptr || out->values == nullptr)) return SS_ERR_INVALID_ARGUMENT;
   if (!aligned(out->keys, 8) || !aligned(out->values, 4) || !aligned(out->tile_ranges, 4))
     return SS_ERR_INVALID_ARGUMENT;
-  const DfLayout lay = make_df_layout(static_cast<uint32_t>(b.n), n_frames, cap, b.tiles, o, b.max_n, b.max_tiles);
-  if (workspace == nullptr || !aligned(workspace, kAlign) || workspace_bytes < lay.total) return SS_ERR_WORKSPACE;
   const hipStream_t s = static_cast<hipStream_t>(stream);
   Launcher L(s, o.timer);
   DfIO io{b.table.data(), frames, out->keys, out->values, out->tile_ranges, nullptr, nullptr,
           out->num_pairs, out->status, out->frame_pairs, out->frame_pair_base};
-  return run_depth_first(L, lay, o, io, workspace, s);
+  const SortLayout lay = make_sort_layout(static_cast<uint32_t>(b.n), n_frames, cap, b.tiles, o, b.max_n, b.max_tiles,
+                                          b.spread);
+  if (workspace == nullptr || !aligned(workspace, kAlign) || workspace_bytes < lay.df.total) return SS_ERR_WORKSPACE;
+  return lay.spread ? run_spread(L, lay.sp, b.spread, o, io, workspace, s)
+                    : run_depth_first(L, lay.df, o, io, workspace, s);
 }
 
 // Batched sizing: per-frame pair counts only.

@@ -15,6 +15,7 @@
 // tile_base[f] + t and keeps frame-local Gaussian indices as values.
 #include "common.hpp"
 #include "internal.hpp"
+#include "totals.hpp"
 
 namespace ss {
 namespace {
@@ -61,6 +62,7 @@ __global__ void k_put_table(TableChunk c, FrameInfo* __restrict__ table) {
 __global__ __launch_bounds__(kCountKeysThreads) void k_count_keys(CountKeysArgs a) {
   __shared__ FrameInfo s_tab[kMaxFrames];
   __shared__ uint32_t s_hist[4 * 256];
+  __shared__ uint32_t s_span[2 * 256];
   __shared__ unsigned long long s_fm[kMaxFrames];
   __shared__ unsigned long long s_tmp[kCountKeysThreads / kWave];
   const uint32_t tid = threadIdx.x;
@@ -69,6 +71,7 @@ __global__ __launch_bounds__(kCountKeysThreads) void k_count_keys(CountKeysArgs 
     s_fm[i] = 0;
   }
   for (uint32_t i = tid; i < 4 * 256; i += kCountKeysThreads) s_hist[i] = 0;
+  if (tid < 2 * 256) s_span[tid] = 0;
   __syncthreads();
   const uint32_t base = blockIdx.x * kCountKeysTile;
   const uint32_t last = min(base + kCountKeysTile, a.n) - 1;
@@ -134,6 +137,21 @@ __global__ __launch_bounds__(kCountKeysThreads) void k_count_keys(CountKeysArgs 
       } else {
         tsum += kCulledOne;
       }
+      // the frame's tile columns and rows, as differences: Gaussians per
+      // column (+1 where its columns start, -1 past their end) and pairs per
+      // row (+w, -w); two atomics each whatever the rectangle's size
+      if (a.span != nullptr && cnt != 0) {
+        const uint32_t x0 = static_cast<uint32_t>(rect) & 0xFFFFu, y0 = static_cast<uint32_t>(rect >> 16) & 0xFFFFu;
+        const uint32_t w = static_cast<uint32_t>(rect >> 32) & 0xFFFFu, h = static_cast<uint32_t>(rect >> 48);
+        auto add = [&](uint32_t* sp) {
+          atomicAdd(&sp[x0], 1u);
+          if (x0 + w < 256) atomicAdd(&sp[x0 + w], ~0u);
+          atomicAdd(&sp[256 + y0], w);
+          if (y0 + h < 256) atomicAdd(&sp[256 + y0 + h], 0u - w);
+        };
+        if (one_frame) add(s_span);
+        else add(a.span + (static_cast<size_t>(blockIdx.x % kHistCopies) * a.n_frames + f) * 2 * 256);
+      }
       // per-frame histograms: a workgroup inside one frame flushes its LDS
       // copy below; one that spans frames (at most one per frame boundary
       // for frames of a workgroup or more) adds each Gaussian here
@@ -178,57 +196,11 @@ __global__ __launch_bounds__(kCountKeysThreads) void k_count_keys(CountKeysArgs 
       if (fh != nullptr) atomicAdd(&fh[i], v);
     }
   }
-}
-
-// Pair totals after the count kernel: per frame, the sum of the one-frame
-// count workgroups' totals plus what multi-frame workgroups added directly;
-// then all pairs, num_pairs, the status (bad depth, over 2^32 pairs, over
-// capacity) and the per-frame pair counts and first pairs.  One workgroup of
-// THREADS >= 256 threads; s_fm holds kMaxFrames values.
-template <int THREADS>
-__device__ __forceinline__ void finish_totals(const PairTotalsArgs& a, unsigned long long* s_fm,
-                                              unsigned long long* s_tmp64, uint32_t* s_tmp) {
-  const uint32_t d = threadIdx.x;
-  for (uint32_t f = d; f < a.n_frames; f += THREADS) s_fm[f] = a.totals[1 + f];
-  __syncthreads();
-  for (uint32_t b = d; b < a.count_blocks; b += THREADS) {
-    const unsigned long long t = a.block_total[b];
-    if (t) atomicAdd(&s_fm[a.block_frame[b]], t);
-  }
-  __syncthreads();
-  const unsigned long long fm = d < a.n_frames ? s_fm[d] : 0ull;
-  unsigned long long m;
-  block_exclusive_scan<unsigned long long, THREADS>(fm, s_tmp64, m);
-  if (d == 0) {
-    uint32_t st = SS_OK;
-    if (*a.bad) st = SS_ERR_INVALID_INPUT;
-    else if (m > 0xFFFFFFFFull) st = SS_ERR_OVERFLOW;
-    else if (m > a.capacity) st = SS_ERR_CAPACITY;
-    *a.num_pairs = m > 0xFFFFFFFFull ? 0xFFFFFFFFu : static_cast<uint32_t>(m);
-    if (*a.status == SS_OK) *a.status = st;
-  }
-  if (a.frame_pairs == nullptr && a.seg_base == nullptr) return;
-  const uint32_t f32 = fm > 0xFFFFFFFFull ? 0xFFFFFFFFu : static_cast<uint32_t>(fm);
-  uint32_t all;
-  const uint32_t ex = block_exclusive_scan<uint32_t, THREADS>(f32, s_tmp, all);
-  if (d < a.n_frames) {
-    if (a.frame_pairs) a.frame_pairs[d] = f32;
-    if (a.frame_pair_base) a.frame_pair_base[d] = ex;
-  }
-  if (a.seg_base == nullptr) return;
-  // segmented tile passes (meaningful only while the status stays SS_OK,
-  // i.e. all pairs fit in 32 bits): each frame's first pair and first
-  // workgroup
-  const uint32_t wgs = static_cast<uint32_t>((static_cast<uint64_t>(f32) + a.seg_tile - 1) / a.seg_tile);
-  uint32_t wall;
-  const uint32_t wex = block_exclusive_scan<uint32_t, THREADS>(wgs, s_tmp, wall);
-  if (d < a.n_frames) {
-    a.seg_base[d] = ex;
-    a.seg_wgs[d] = wex;
-  }
-  if (d == 0) {
-    a.seg_base[a.n_frames] = all;
-    a.seg_wgs[a.n_frames] = wall;
+  if (a.span != nullptr && one_frame && tid < 2 * 256) {
+    const uint32_t v = s_span[tid];
+    if (v)
+      atomicAdd(&a.span[(static_cast<size_t>(blockIdx.x % kHistCopies) * a.n_frames + frame_of(s_tab, a.n_frames, base)) *
+                            2 * 256 + tid], v);
   }
 }
 

@@ -37,7 +37,7 @@ struct FrameInfo {
   uint32_t n;            // Gaussians of the frame
   uint32_t tiles_x, tiles_y;
   uint32_t tile_base;    // first global tile id of the frame
-  uint32_t pad;
+  uint32_t col_chunk;    // first workgroup of the frame in the column pass (spread.hip)
   const ss_gaussian2d* gaussians;
 };
 static_assert(sizeof(FrameInfo) == 32, "frame table entry");
@@ -64,6 +64,74 @@ __device__ __forceinline__ bool packed_depth_trimmed(uint32_t top_max, uint32_t 
   const uint64_t span = top_max >= top_min ? static_cast<uint64_t>(top_max - top_min + 1) : 1ull;
   return dbits >= 32 || (span << 24) <= (1ull << dbits);
 }
+
+// Pair totals: per frame (sum of the count workgroups' totals), all frames,
+// and from them num_pairs and the status word.
+struct PairTotalsArgs {
+  const unsigned long long* totals;       // [1 + n_frames], from multi-frame count workgroups
+  const unsigned long long* block_total;  // [count_blocks]
+  const uint32_t* block_frame;            // [count_blocks]
+  uint32_t count_blocks;
+  const uint32_t* bad;
+  uint32_t n_frames;
+  uint32_t capacity;
+  uint32_t* num_pairs;
+  uint32_t* status;            // set only while it still reads SS_OK
+  uint32_t* frame_pairs;       // optional
+  uint32_t* frame_pair_base;   // optional
+  // segmented tile passes: [n_frames + 1] first pair and first tile
+  // workgroup of each frame (workgroups of seg_tile pairs), or NULL
+  uint32_t* seg_base;
+  uint32_t* seg_wgs;
+  uint32_t seg_tile;
+};
+
+// A frame's plan for the spread passes (spread.hip), kPlanWords per frame:
+// exclusive prefixes, inside the frame, of the column items before each tile
+// column, of the pairs before each tile row and of the row pass's workgroups
+// before each column; entry tiles_x (tiles_y) of each holds the frame's total.
+constexpr uint32_t kPlanStride = 257;
+constexpr uint32_t kPlanRow = kPlanStride, kPlanChunk = 2 * kPlanStride;
+constexpr uint32_t kPlanWords = 3 * kPlanStride;
+
+// Gaussians per workgroup of the column pass.
+constexpr uint32_t kColumnItems = 2048;
+
+// A workgroup of a spread pass: its items, its frame and the first workgroup
+// of its look-back chain (the frame's first).
+struct SpreadChunk {
+  uint32_t base;        // first item
+  uint32_t count;       // items | the row pass's column << 16
+  uint32_t frame : 16, col_first : 16;  // col_first: first workgroup of its column
+  uint32_t first;
+};
+static_assert(sizeof(SpreadChunk) == 16, "one 16-byte load");
+
+// Work that extra workgroups of the first three depth passes do beside the
+// pass, so that it costs no launch (workgroups from side_first on):
+//   kPlan: one per frame, its plan from the span histograms and its column
+//     chunks;
+//   kTotals: one, the pair totals and the status, and the frames' first column
+//     items and row chunks;
+//   kRows: one per frame, its row chunks.
+struct SideWork {
+  enum Kind : uint32_t { kNone = 0, kPlan = 1, kTotals = 2, kRows = 3 };
+  uint32_t kind;
+  uint32_t side_first;
+  uint32_t row_items;        // column items per workgroup of the row pass
+  uint32_t n_frames;
+  const FrameInfo* table;
+  const uint32_t* span;      // [kHistCopies][n_frames][2][256]
+  uint32_t* plan;            // [n_frames][kPlanWords]
+  uint32_t* item_base;       // [n_frames + 1] first column item of each frame
+  uint32_t* row_chunk;       // [n_frames + 1] first row-pass workgroup of each frame
+  const uint32_t* culled;    // digit 255 of the top depth byte, [copy][frame], culled_copy and
+  uint32_t culled_copy, culled_frame;  // culled_frame words apart
+  SpreadChunk* col_chunks;   // column chunks of all frames (frame f's from its col_chunk)
+  SpreadChunk* row_chunks;   // row chunks of all frames
+  const uint32_t* status;    // kRows
+  PairTotalsArgs totals;     // (its seg_base: first pair of each frame)
+};
 
 struct PassArgs {
   const void* kin;            // uint64_t or uint32_t keys
@@ -137,6 +205,10 @@ struct PassArgs {
   // the frame's first Gaussian; the workgroups past the frames' tiles exit.
   bool depth_seg;
   uint32_t n_frames;
+  // 32-bit keys: work of extra workgroups beside the pass.  A launch whose
+  // side work sets the status does not read it on entry: its other workgroups
+  // must all run.
+  SideWork side;
   // Bounded waits: polls before SS_ERR_TIMEOUT (kSpinLimit when 0).  fault:
   // SS_FAULT_* test hook (SS_FAULT_WITHHOLD_BASES: the chain's publishing
   // workgroups publish nothing, so every tile's wait for its bases times out).
@@ -180,32 +252,14 @@ struct CountKeysArgs {
   uint32_t* hist;           // zeroed [kHistCopies][4][256] depth digit histograms
   uint32_t* frame_hist;     // or NULL; else also zeroed [kHistCopies][n_frames][4][256]: the
                             // same per frame (the segmented depth sort)
+  uint32_t* span;           // or NULL; else zeroed [kHistCopies][n_frames][2][256], every frame of at
+                            // most 256 tiles per axis: per tile column the change of the number of
+                            // Gaussians meeting it, per tile row that of the pairs in it
   unsigned long long* totals;  // zeroed [1 + n_frames]: pairs per frame at [1 + f]
                                // (only workgroups that span several frames add here)
   unsigned long long* block_total;  // [nblocks] pairs of a one-frame workgroup, else 0
   uint32_t* block_frame;    // [nblocks] that workgroup's frame
   uint32_t* bad;            // zeroed flag: a touching Gaussian has a bad depth
-};
-
-// Pair totals: per frame (sum of the count workgroups' totals), all frames,
-// and from them num_pairs and the status word.
-struct PairTotalsArgs {
-  const unsigned long long* totals;       // [1 + n_frames], from multi-frame count workgroups
-  const unsigned long long* block_total;  // [count_blocks]
-  const uint32_t* block_frame;            // [count_blocks]
-  uint32_t count_blocks;
-  const uint32_t* bad;
-  uint32_t n_frames;
-  uint32_t capacity;
-  uint32_t* num_pairs;
-  uint32_t* status;            // set only while it still reads SS_OK
-  uint32_t* frame_pairs;       // optional
-  uint32_t* frame_pair_base;   // optional
-  // segmented tile passes: [n_frames + 1] first pair and first tile
-  // workgroup of each frame (workgroups of seg_tile pairs), or NULL
-  uint32_t* seg_base;
-  uint32_t* seg_wgs;
-  uint32_t seg_tile;
 };
 
 struct ExpandArgs {
@@ -255,6 +309,36 @@ struct ExpandArgs {
   const uint32_t* culled;
   uint32_t culled_stride;
 };
+
+// Spread passes (see spread.hip).
+struct SpreadArgs {
+  const FrameInfo* table;
+  uint32_t max_digits;        // most tile columns (rows) of a frame
+  uint32_t lb_stride;         // words per workgroup in lookback
+  const SpreadChunk* chunks;  // of this pass
+  const uint32_t* num_chunks; // row pass: how many there are (its grid is a bound)
+  const uint32_t* plan;       // [n_frames][kPlanWords]
+  const uint32_t* item_base;  // [n_frames + 1] first column item of each frame
+  const uint32_t* pair_base;  // [n_frames + 1] first pair of each frame
+  uint32_t* lookback;         // zeroed [workgroups][lb_stride]
+  uint32_t* status;
+  uint32_t capacity;          // pairs (and column items) that may be written
+  uint32_t spin_limit, fault;
+  // column pass: the Gaussians in depth order, frame-major
+  const uint32_t* key;        // depth bits
+  const uint32_t* val;        // global index
+  const uint32_t* rect;       // packed rectangle, in depth order or (rect_by_index) by global index
+  bool rect_by_index;
+  // column items: out of the column pass, in of the row pass
+  uint64_t* item;             // index << 32 | depth bits
+  uint16_t* item_rows;        // first tile row | (rows - 1) << 8
+  // row pass: the sorted pairs and the ranges
+  uint64_t* keys;
+  uint32_t* values;
+  uint32_t* ranges;
+};
+hipError_t launch_columns(const SpreadArgs& a, uint32_t nblocks, hipStream_t s);
+hipError_t launch_rows(const SpreadArgs& a, uint32_t row_items, uint32_t nblocks, hipStream_t s);
 
 hipError_t launch_put_table(const TableChunk& c, FrameInfo* table, hipStream_t s);
 hipError_t launch_count_keys(const CountKeysArgs& a, hipStream_t s);

@@ -15,6 +15,7 @@
 // a pair whose tile differs from its predecessor's starts a range.
 #include "common.hpp"
 #include "internal.hpp"
+#include "totals.hpp"
 
 namespace ss {
 namespace {
@@ -506,13 +507,122 @@ __device__ __forceinline__ void publish_bases_seg(const PassArgs& a, uint32_t f,
   }
 }
 
+// A frame's plan (SideWork::kPlan): prefixes over the tile columns and rows
+// from the span histograms, whose running sums are the Gaussians per column
+// and the pairs per row.  A column without items still gets one workgroup of
+// the row pass, which writes its tiles' ranges.
+template <int THREADS>
+__device__ __forceinline__ void side_plan(const SideWork& s, uint32_t f, uint32_t* s_tmp) {
+  const uint32_t d = threadIdx.x;
+  const uint32_t tx = s.table[f].tiles_x, ty = s.table[f].tiles_y;
+  uint32_t dx = 0, dy = 0;
+  if (d < 256) {
+#pragma unroll
+    for (uint32_t c = 0; c < kHistCopies; ++c) {
+      const uint32_t* h = s.span + (static_cast<size_t>(c) * s.n_frames + f) * 2 * 256;
+      dx += h[d];
+      dy += h[256 + d];
+    }
+  }
+  uint32_t all, items, pairs, chunks;
+  const uint32_t nx = block_exclusive_scan<uint32_t, THREADS>(dx, s_tmp, all) + dx;  // modulo 2^32: counts
+  const uint32_t ny = block_exclusive_scan<uint32_t, THREADS>(dy, s_tmp, all) + dy;
+  const uint32_t cx = d < tx ? nx : 0u, cy = d < ty ? ny : 0u;
+  const uint32_t ch = d < tx ? (cx > s.row_items ? (cx - 1) / s.row_items + 1 : 1u) : 0u;
+  const uint32_t ex = block_exclusive_scan<uint32_t, THREADS>(cx, s_tmp, items);
+  const uint32_t ey = block_exclusive_scan<uint32_t, THREADS>(cy, s_tmp, pairs);
+  const uint32_t ec = block_exclusive_scan<uint32_t, THREADS>(ch, s_tmp, chunks);
+  uint32_t* p = s.plan + static_cast<size_t>(f) * kPlanWords;
+  if (d < tx) {
+    p[d] = ex;
+    p[kPlanChunk + d] = ec;
+  }
+  if (d < ty) p[kPlanRow + d] = ey;
+  if (d == 0) {
+    p[tx] = items;
+    p[kPlanRow + ty] = pairs;
+    p[kPlanChunk + tx] = chunks;
+  }
+  // column chunks: the frame's live Gaussians (the culled sort last)
+  uint32_t culled = 0;
+#pragma unroll
+  for (uint32_t c = 0; c < kHistCopies; ++c)
+    culled += s.culled[static_cast<size_t>(c) * s.culled_copy + static_cast<size_t>(f) * s.culled_frame];
+  const uint32_t n = s.table[f].n, live = n - culled, g0 = s.table[f].gauss_base, c0 = s.table[f].col_chunk;
+  for (uint32_t k = d; static_cast<uint64_t>(k) * kColumnItems < n; k += THREADS) {
+    const uint32_t at = k * kColumnItems;
+    SpreadChunk ch{};
+    ch.base = g0 + at;
+    ch.count = at < live ? (live - at < kColumnItems ? live - at : kColumnItems) : 0u;
+    ch.frame = f;
+    ch.first = c0;
+    s.col_chunks[c0 + k] = ch;
+  }
+}
+
+// SideWork::kRows, after the totals: the frame's row chunks, column by column
+// (a wave per column).  Only for a status of SS_OK, which bounds their number.
+template <int THREADS>
+__device__ __forceinline__ void side_rows(const SideWork& s, uint32_t f) {
+  if (*s.status != SS_OK) return;
+  const uint32_t* p = s.plan + static_cast<size_t>(f) * kPlanWords;
+  const uint32_t tx = s.table[f].tiles_x, c0 = s.row_chunk[f], i0 = s.item_base[f];
+  for (uint32_t col = threadIdx.x / kWave; col < tx; col += THREADS / kWave) {
+    const uint32_t k0 = p[kPlanChunk + col], k1 = p[kPlanChunk + col + 1], b = p[col], e = p[col + 1];
+    for (uint32_t k = lane_id(); k < k1 - k0; k += kWave) {
+      const uint32_t at = k * s.row_items, left = e - b - at;   // (a column without items: none left)
+      SpreadChunk ch{};
+      ch.base = i0 + b + at;
+      ch.count = (left < s.row_items ? left : s.row_items) | col << 16;
+      ch.frame = f;
+      ch.col_first = k == 0;
+      ch.first = c0;
+      s.row_chunks[c0 + k0 + k] = ch;
+    }
+  }
+}
+
+// SideWork::kTotals, after every frame's plan: pair totals and status, the
+// frames' first pairs, column items and row-pass workgroups.
+template <int THREADS>
+__device__ __forceinline__ void side_totals(const SideWork& s, unsigned long long* s_fm, unsigned long long* s_tmp64,
+                                            uint32_t* s_tmp) {
+  finish_totals<THREADS>(s.totals, s_fm, s_tmp64, s_tmp);
+  const uint32_t d = threadIdx.x;
+  uint32_t items = 0, chunks = 0, all;
+  if (d < s.n_frames) {
+    const uint32_t* p = s.plan + static_cast<size_t>(d) * kPlanWords;
+    const uint32_t tx = s.table[d].tiles_x;
+    items = p[tx];
+    chunks = p[kPlanChunk + tx];
+  }
+  const uint32_t ei = block_exclusive_scan<uint32_t, THREADS>(items, s_tmp, all);
+  if (d < s.n_frames) s.item_base[d] = ei;
+  if (d == 0) s.item_base[s.n_frames] = all;
+  const uint32_t ec = block_exclusive_scan<uint32_t, THREADS>(chunks, s_tmp, all);
+  if (d < s.n_frames) s.row_chunk[d] = ec;
+  if (d == 0) s.row_chunk[s.n_frames] = all;
+}
+
 // DROP (32-bit keys, the depth sort's first pass): may drop the culled
 // Gaussians (the decision is known only after the loads).  Workgroup b is
 // tile b (after the publishing workgroups).
 template <typename K, int RB, int ITEMS, int THREADS, int MODE, bool DROP>
 __global__ __launch_bounds__(THREADS) void k_onesweep(PassArgs a) {
   __shared__ PassSmem<K, RB, ITEMS, THREADS, MODE> sm;
-  if (a.status && *a.status != SS_OK) return;
+  if constexpr (sizeof(K) == 4) {
+    if (a.side.kind != SideWork::kNone && blockIdx.x >= a.side.side_first) {
+      static_assert(sizeof(sm.buf) >= kMaxFrames * sizeof(unsigned long long), "totals in the permute buffer");
+      uint32_t* s_tmp = reinterpret_cast<uint32_t*>(sm.tmp);
+      if (a.side.kind == SideWork::kPlan) side_plan<THREADS>(a.side, blockIdx.x - a.side.side_first, s_tmp);
+      else if (a.side.kind == SideWork::kRows) side_rows<THREADS>(a.side, blockIdx.x - a.side.side_first);
+      else side_totals<THREADS>(a.side, reinterpret_cast<unsigned long long*>(sm.buf), sm.tmp, s_tmp);
+      return;
+    }
+    if (a.status && a.side.kind != SideWork::kTotals && *a.status != SS_OK) return;
+  } else {
+    if (a.status && *a.status != SS_OK) return;
+  }
   onesweep_body<K, RB, ITEMS, THREADS, MODE, DROP>(a, sm, blockIdx.x);
   if constexpr (sizeof(K) == 4) {
     if (a.depth_top_out != nullptr && blockIdx.x == 0) store_depth_top<THREADS>(a, sm.dstart);
@@ -681,6 +791,10 @@ hipError_t pass_launch(const PassArgs& a, uint32_t nblocks, hipStream_t s) {
   }
   if (a.tickets != nullptr) return hipErrorInvalidValue;  // persistent: 512-thread 64-bit passes only
   if constexpr (sizeof(K) == 4) {
+    if (a.side.kind != SideWork::kNone) {
+      if (a.side.side_first != grid) return hipErrorInvalidValue;
+      grid += a.side.kind == SideWork::kTotals ? 1u : a.side.n_frames;
+    }
     if (a.culled != nullptr) {
       hipLaunchKernelGGL((k_onesweep<K, RB, ITEMS, THREADS, MODE, true>), dim3(grid), dim3(THREADS), 0, s, a);
       return hipGetLastError();
