@@ -567,10 +567,7 @@ ss_status run_chain(Launcher& L, uint32_t kind, const PassChain& c, hipStream_t 
         a.depth_top_out = c.depth_top_out;
         a.hist_top = c.hist_top;
       }
-      if (c.side != nullptr && p < 3) {
-        a.side = c.side[p];
-        a.side.side_first = c.nblocks;
-      }
+      if (c.side != nullptr && p < 3) a.side = c.side[p];
       a.spin_limit = c.spin_limit;
       a.fault = c.fault;
       a.tickets = c.tickets ? c.tickets + p : nullptr;

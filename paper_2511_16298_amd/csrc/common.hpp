@@ -74,6 +74,27 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, uint64_t lanes) {
   return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
+// XCD-aware tile order.  Workgroups are handed to the eight XCDs in turn, each
+// with an L2 of its own; in groups of 8 << LOG workgroups, those of one XCD
+// take 1 << LOG consecutive tiles, so that the short runs which neighbouring
+// tiles write next to each other meet in one L2 instead of leaving as partial
+// lines.  A tile may then wait on a tile of a later workgroup, but only inside
+// its group: an XCD's own workgroups still take rising tiles, so the lowest
+// unfinished tile's workgroup finds a slot once the lower tiles before it on
+// its XCD finish, and a group is far smaller than what the GPU holds at once.
+// The grid is rounded up to whole groups; tiles past the last one exit.
+template <uint32_t LOG>
+__device__ __forceinline__ uint32_t xcd_order(uint32_t b) {
+  constexpr uint32_t kGroup = 8u << LOG;
+  const uint32_t r = b % kGroup;
+  return b - r + ((r % 8) << LOG) + r / 8;
+}
+template <uint32_t LOG>
+constexpr uint32_t xcd_grid(uint32_t blocks) {
+  constexpr uint32_t kGroup = LOG == 0 ? 1u : 8u << LOG;
+  return (blocks + kGroup - 1) / kGroup * kGroup;
+}
+
 // Cross-workgroup words are read and written with device-scope atomics so
 // they are coherent across the XCDs' separate L2 caches.
 __device__ __forceinline__ uint32_t ld_agent(const uint32_t* p) {

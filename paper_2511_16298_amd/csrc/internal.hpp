@@ -117,7 +117,7 @@ static_assert(sizeof(SpreadChunk) == 16, "one 16-byte load");
 struct SideWork {
   enum Kind : uint32_t { kNone = 0, kPlan = 1, kTotals = 2, kRows = 3 };
   uint32_t kind;
-  uint32_t side_first;
+  uint32_t side_first;       // (set by the launch)
   uint32_t row_items;        // column items per workgroup of the row pass
   uint32_t n_frames;
   const FrameInfo* table;

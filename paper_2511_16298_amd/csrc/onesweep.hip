@@ -604,9 +604,20 @@ __device__ __forceinline__ void side_totals(const SideWork& s, unsigned long lon
   if (d == 0) s.row_chunk[s.n_frames] = all;
 }
 
+// Consecutive tiles per XCD of a pass (log2).  8,192-item tiles with values
+// split into 256 digits write runs of 32 items, whose lines they share with
+// the tiles before and after: eight tiles per XCD and group took the key +
+// value passes over 17M pairs from 760 to 693 us (four: 704, sixteen: 697,
+// thirty-two: 713) and the depth passes of the 6M-Gaussian frame and of the
+// 64-frame batch from 168 to 156 and from 756 to 690 us.  The 4,096-item
+// depth tiles of smaller frames lose (full HD 1M, 245 tiles: 144.5 -> 148.4
+// us a frame, the XCDs' shares being less even), so they stay in order.
+template <int ITEMS, int THREADS, int MODE>
+constexpr uint32_t kTileOrder = MODE == kPassKV && ITEMS == 16 && THREADS == 512 ? 3 : 0;
+
 // DROP (32-bit keys, the depth sort's first pass): may drop the culled
 // Gaussians (the decision is known only after the loads).  Workgroup b is
-// tile b (after the publishing workgroups).
+// tile b, or the tile the order gives it (after the publishing workgroups).
 template <typename K, int RB, int ITEMS, int THREADS, int MODE, bool DROP>
 __global__ __launch_bounds__(THREADS) void k_onesweep(PassArgs a) {
   __shared__ PassSmem<K, RB, ITEMS, THREADS, MODE> sm;
@@ -623,7 +634,8 @@ __global__ __launch_bounds__(THREADS) void k_onesweep(PassArgs a) {
   } else {
     if (a.status && *a.status != SS_OK) return;
   }
-  onesweep_body<K, RB, ITEMS, THREADS, MODE, DROP>(a, sm, blockIdx.x);
+  constexpr uint32_t kOrder = kTileOrder<ITEMS, THREADS, MODE>;
+  onesweep_body<K, RB, ITEMS, THREADS, MODE, DROP>(a, sm, kOrder == 0 ? blockIdx.x : xcd_order<kOrder>(blockIdx.x));
   if constexpr (sizeof(K) == 4) {
     if (a.depth_top_out != nullptr && blockIdx.x == 0) store_depth_top<THREADS>(a, sm.dstart);
   }
@@ -777,7 +789,7 @@ uint32_t resident_workgroups() {
 }
 
 template <typename K, int RB, int ITEMS, int THREADS, int MODE>
-hipError_t pass_launch(const PassArgs& a, uint32_t nblocks, hipStream_t s) {
+hipError_t pass_launch(PassArgs a, uint32_t nblocks, hipStream_t s) {
   const uint32_t publishers = a.publish_passes == 0 ? 0u : a.seg_wgs != nullptr ? a.seg_frames : 1u;
   uint32_t grid = nblocks + (sizeof(K) == 8 ? publishers : 0u);
   if constexpr (sizeof(K) == 8 && THREADS == 512) {
@@ -790,9 +802,10 @@ hipError_t pass_launch(const PassArgs& a, uint32_t nblocks, hipStream_t s) {
     }
   }
   if (a.tickets != nullptr) return hipErrorInvalidValue;  // persistent: 512-thread 64-bit passes only
+  grid = xcd_grid<kTileOrder<ITEMS, THREADS, MODE>>(grid);
   if constexpr (sizeof(K) == 4) {
     if (a.side.kind != SideWork::kNone) {
-      if (a.side.side_first != grid) return hipErrorInvalidValue;
+      a.side.side_first = grid;
       grid += a.side.kind == SideWork::kTotals ? 1u : a.side.n_frames;
     }
     if (a.culled != nullptr) {
