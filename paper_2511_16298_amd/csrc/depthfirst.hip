@@ -59,10 +59,12 @@ __global__ void k_put_table(TableChunk c, FrameInfo* __restrict__ table) {
 // Step 1.  2048 Gaussians per workgroup of 512 threads, loaded striped
 // (coalesced 16-byte loads).  No scan here: only totals (all pairs and per
 // frame) by atomics, and the four depth-digit histograms of the Gaussian sort.
+// SPAN: also the column and row histograms of the spread passes (a.span).
+template <bool SPAN>
 __global__ __launch_bounds__(kCountKeysThreads) void k_count_keys(CountKeysArgs a) {
   __shared__ FrameInfo s_tab[kMaxFrames];
   __shared__ uint32_t s_hist[4 * 256];
-  __shared__ uint32_t s_span[2 * 256];
+  __shared__ uint32_t s_span[SPAN ? 2 * 256 : 1];
   __shared__ unsigned long long s_fm[kMaxFrames];
   __shared__ unsigned long long s_tmp[kCountKeysThreads / kWave];
   const uint32_t tid = threadIdx.x;
@@ -71,7 +73,7 @@ __global__ __launch_bounds__(kCountKeysThreads) void k_count_keys(CountKeysArgs 
     s_fm[i] = 0;
   }
   for (uint32_t i = tid; i < 4 * 256; i += kCountKeysThreads) s_hist[i] = 0;
-  if (tid < 2 * 256) s_span[tid] = 0;
+  if (SPAN && tid < 2 * 256) s_span[tid] = 0;
   __syncthreads();
   const uint32_t base = blockIdx.x * kCountKeysTile;
   const uint32_t last = min(base + kCountKeysTile, a.n) - 1;
@@ -140,7 +142,7 @@ __global__ __launch_bounds__(kCountKeysThreads) void k_count_keys(CountKeysArgs 
       // the frame's tile columns and rows, as differences: Gaussians per
       // column (+1 where its columns start, -1 past their end) and pairs per
       // row (+w, -w); two atomics each whatever the rectangle's size
-      if (a.span != nullptr && cnt != 0) {
+      if (SPAN && cnt != 0) {
         const uint32_t x0 = static_cast<uint32_t>(rect) & 0xFFFFu, y0 = static_cast<uint32_t>(rect >> 16) & 0xFFFFu;
         const uint32_t w = static_cast<uint32_t>(rect >> 32) & 0xFFFFu, h = static_cast<uint32_t>(rect >> 48);
         auto add = [&](uint32_t* sp) {
@@ -196,7 +198,7 @@ __global__ __launch_bounds__(kCountKeysThreads) void k_count_keys(CountKeysArgs 
       if (fh != nullptr) atomicAdd(&fh[i], v);
     }
   }
-  if (a.span != nullptr && one_frame && tid < 2 * 256) {
+  if (SPAN && one_frame && tid < 2 * 256) {
     const uint32_t v = s_span[tid];
     if (v)
       atomicAdd(&a.span[(static_cast<size_t>(blockIdx.x % kHistCopies) * a.n_frames + frame_of(s_tab, a.n_frames, base)) *
@@ -594,7 +596,8 @@ hipError_t launch_put_table(const TableChunk& c, FrameInfo* table, hipStream_t s
 hipError_t launch_count_keys(const CountKeysArgs& a, hipStream_t s) {
   const uint32_t blocks = (a.n + kCountKeysTile - 1) / kCountKeysTile;
   if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_count_keys, dim3(blocks), dim3(kCountKeysThreads), 0, s, a);
+  if (a.span != nullptr) hipLaunchKernelGGL(k_count_keys<true>, dim3(blocks), dim3(kCountKeysThreads), 0, s, a);
+  else hipLaunchKernelGGL(k_count_keys<false>, dim3(blocks), dim3(kCountKeysThreads), 0, s, a);
   return hipGetLastError();
 }
 

@@ -108,16 +108,15 @@ struct SpreadChunk {
 static_assert(sizeof(SpreadChunk) == 16, "one 16-byte load");
 
 // Work that extra workgroups of the first three depth passes do beside the
-// pass, so that it costs no launch (workgroups from side_first on):
+// pass, so that it costs no launch:
 //   kPlan: one per frame, its plan from the span histograms and its column
 //     chunks;
 //   kTotals: one, the pair totals and the status, and the frames' first column
 //     items and row chunks;
 //   kRows: one per frame, its row chunks.
 struct SideWork {
-  enum Kind : uint32_t { kNone = 0, kPlan = 1, kTotals = 2, kRows = 3 };
+  enum Kind : uint32_t { kPlan = 1, kTotals = 2, kRows = 3 };
   uint32_t kind;
-  uint32_t side_first;       // (set by the launch)
   uint32_t row_items;        // column items per workgroup of the row pass
   uint32_t n_frames;
   const FrameInfo* table;
@@ -205,10 +204,6 @@ struct PassArgs {
   // the frame's first Gaussian; the workgroups past the frames' tiles exit.
   bool depth_seg;
   uint32_t n_frames;
-  // 32-bit keys: work of extra workgroups beside the pass.  A launch whose
-  // side work sets the status does not read it on entry: its other workgroups
-  // must all run.
-  SideWork side;
   // Bounded waits: polls before SS_ERR_TIMEOUT (kSpinLimit when 0).  fault:
   // SS_FAULT_* test hook (SS_FAULT_WITHHOLD_BASES: the chain's publishing
   // workgroups publish nothing, so every tile's wait for its bases times out).
@@ -364,6 +359,9 @@ hipError_t launch_hist(const HistArgs& a, int radix_bits, hipStream_t s);
 constexpr int kPassKV = 0, kPassItems = 1, kPassUnpack = 2;
 hipError_t launch_pass(const PassArgs& a, int key_bytes, int radix_bits, int items, int threads, uint32_t nblocks,
                        hipStream_t s, int mode = kPassKV);
+// A depth pass (32-bit keys) with side work beside it.
+hipError_t launch_depth_side(const PassArgs& a, const SideWork& side, int items, int threads, uint32_t nblocks,
+                             hipStream_t s);
 // Whether a packed pass of this shape is compiled.
 bool packed_pass_supported(int radix_bits, int items, int threads);
 // After a last pass with fused ranges: each digit's first pair (its

@@ -621,24 +621,33 @@ constexpr uint32_t kTileOrder = MODE == kPassKV && ITEMS == 16 && THREADS == 512
 template <typename K, int RB, int ITEMS, int THREADS, int MODE, bool DROP>
 __global__ __launch_bounds__(THREADS) void k_onesweep(PassArgs a) {
   __shared__ PassSmem<K, RB, ITEMS, THREADS, MODE> sm;
-  if constexpr (sizeof(K) == 4) {
-    if (a.side.kind != SideWork::kNone && blockIdx.x >= a.side.side_first) {
-      static_assert(sizeof(sm.buf) >= kMaxFrames * sizeof(unsigned long long), "totals in the permute buffer");
-      uint32_t* s_tmp = reinterpret_cast<uint32_t*>(sm.tmp);
-      if (a.side.kind == SideWork::kPlan) side_plan<THREADS>(a.side, blockIdx.x - a.side.side_first, s_tmp);
-      else if (a.side.kind == SideWork::kRows) side_rows<THREADS>(a.side, blockIdx.x - a.side.side_first);
-      else side_totals<THREADS>(a.side, reinterpret_cast<unsigned long long*>(sm.buf), sm.tmp, s_tmp);
-      return;
-    }
-    if (a.status && a.side.kind != SideWork::kTotals && *a.status != SS_OK) return;
-  } else {
-    if (a.status && *a.status != SS_OK) return;
-  }
+  if (a.status && *a.status != SS_OK) return;
   constexpr uint32_t kOrder = kTileOrder<ITEMS, THREADS, MODE>;
   onesweep_body<K, RB, ITEMS, THREADS, MODE, DROP>(a, sm, kOrder == 0 ? blockIdx.x : xcd_order<kOrder>(blockIdx.x));
   if constexpr (sizeof(K) == 4) {
     if (a.depth_top_out != nullptr && blockIdx.x == 0) store_depth_top<THREADS>(a, sm.dstart);
   }
+}
+
+// A depth pass of the spread path, with side work in the workgroups from
+// side_first on.  Where that sets the status (kTotals), the pass's own
+// workgroups do not read it on entry: they must all run.
+template <int ITEMS, int THREADS, bool DROP>
+__global__ __launch_bounds__(THREADS) void k_depth_side(PassArgs a, SideWork side, uint32_t side_first) {
+  __shared__ PassSmem<uint32_t, 8, ITEMS, THREADS, kPassKV> sm;
+  if (blockIdx.x >= side_first) {
+    static_assert(sizeof(sm.buf) >= kMaxFrames * sizeof(unsigned long long), "totals in the permute buffer");
+    uint32_t* s_tmp = reinterpret_cast<uint32_t*>(sm.tmp);
+    const uint32_t b = blockIdx.x - side_first;
+    if (side.kind == SideWork::kPlan) side_plan<THREADS>(side, b, s_tmp);
+    else if (side.kind == SideWork::kRows) side_rows<THREADS>(side, b);
+    else side_totals<THREADS>(side, reinterpret_cast<unsigned long long*>(sm.buf), sm.tmp, s_tmp);
+    return;
+  }
+  if (side.kind != SideWork::kTotals && *a.status != SS_OK) return;
+  constexpr uint32_t kOrder = kTileOrder<ITEMS, THREADS, kPassKV>;
+  onesweep_body<uint32_t, 8, ITEMS, THREADS, kPassKV, DROP>(
+      a, sm, kOrder == 0 ? blockIdx.x : xcd_order<kOrder>(blockIdx.x));
 }
 
 // Persistent form (64-bit keys, 512 threads, a.tickets): tickets in order
@@ -789,7 +798,7 @@ uint32_t resident_workgroups() {
 }
 
 template <typename K, int RB, int ITEMS, int THREADS, int MODE>
-hipError_t pass_launch(PassArgs a, uint32_t nblocks, hipStream_t s) {
+hipError_t pass_launch(const PassArgs& a, uint32_t nblocks, hipStream_t s) {
   const uint32_t publishers = a.publish_passes == 0 ? 0u : a.seg_wgs != nullptr ? a.seg_frames : 1u;
   uint32_t grid = nblocks + (sizeof(K) == 8 ? publishers : 0u);
   if constexpr (sizeof(K) == 8 && THREADS == 512) {
@@ -804,16 +813,23 @@ hipError_t pass_launch(PassArgs a, uint32_t nblocks, hipStream_t s) {
   if (a.tickets != nullptr) return hipErrorInvalidValue;  // persistent: 512-thread 64-bit passes only
   grid = xcd_grid<kTileOrder<ITEMS, THREADS, MODE>>(grid);
   if constexpr (sizeof(K) == 4) {
-    if (a.side.kind != SideWork::kNone) {
-      a.side.side_first = grid;
-      grid += a.side.kind == SideWork::kTotals ? 1u : a.side.n_frames;
-    }
     if (a.culled != nullptr) {
       hipLaunchKernelGGL((k_onesweep<K, RB, ITEMS, THREADS, MODE, true>), dim3(grid), dim3(THREADS), 0, s, a);
       return hipGetLastError();
     }
   }
   hipLaunchKernelGGL((k_onesweep<K, RB, ITEMS, THREADS, MODE, false>), dim3(grid), dim3(THREADS), 0, s, a);
+  return hipGetLastError();
+}
+
+template <int ITEMS, int THREADS>
+hipError_t depth_side_launch(const PassArgs& a, const SideWork& side, uint32_t nblocks, hipStream_t s) {
+  const uint32_t first = xcd_grid<kTileOrder<ITEMS, THREADS, kPassKV>>(nblocks);
+  const uint32_t grid = first + (side.kind == SideWork::kTotals ? 1u : side.n_frames);
+  if (a.culled != nullptr)
+    hipLaunchKernelGGL((k_depth_side<ITEMS, THREADS, true>), dim3(grid), dim3(THREADS), 0, s, a, side, first);
+  else
+    hipLaunchKernelGGL((k_depth_side<ITEMS, THREADS, false>), dim3(grid), dim3(THREADS), 0, s, a, side, first);
   return hipGetLastError();
 }
 
@@ -936,6 +952,14 @@ hipError_t launch_pass(const PassArgs& a, int key_bytes, int radix_bits, int ite
   SS_PACKED_CASE(6, 16) SS_PACKED_CASE(6, 8) SS_PACKED_CASE(5, 16) SS_PACKED_CASE(5, 8)
   SS_PACKED_CASE(4, 16) SS_PACKED_CASE(4, 8)
 #undef SS_PACKED_CASE
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_depth_side(const PassArgs& a, const SideWork& side, int items, int threads, uint32_t nblocks,
+                             hipStream_t s) {
+  if (a.status == nullptr || nblocks == 0) return hipErrorInvalidValue;
+  if (items == 16 && threads == 512) return depth_side_launch<16, 512>(a, side, nblocks, s);
+  if (items == 4 && threads == 1024) return depth_side_launch<4, 1024>(a, side, nblocks, s);
   return hipErrorInvalidValue;
 }
 

@@ -19,7 +19,7 @@
 // the digits [lo, hi):
 //   1. a bit matrix in LDS, one row of a bit per item for each digit: every
 //      item toggles its bit in the rows where its interval starts and ends,
-//      whatever its length.  The rows are cut into blocks, one per half-wave;
+//      whatever its length.  The rows are cut into blocks, each walked by the lanes of one row's words;
 //      an item whose interval runs on into a block sets its bit in the
 //      block's opening word.
 //   2. the running XOR down a block's rows, from its opening word, is the
@@ -72,7 +72,7 @@ struct Shape {
   static constexpr uint32_t kBlocks = THREADS / kWords;    // blocks of rows, each walked by kWords lanes
   // Outputs listed per round; a workgroup with more takes further rounds.
   static constexpr uint32_t kSlots = 3 * kItems;
-  static_assert(kWords == 32 || kWords == 64, "a row's lanes are half a wave or a wave");
+  static_assert(kWords == 16 || kWords == 32 || kWords == 64, "a row's lanes are a DPP row, half a wave or a wave");
   static_assert(kBlocks == 16, "at most 16 rows a block");
   static_assert(kBlocks * kRowStride * sizeof(uint64_t) <= kSlots * sizeof(uint16_t), "opening words in the list's place");
 };
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(THREADS, ROWS ? 8 : 6) void k_spread(SpreadArgs a) 
       x += dpp0<kDppRowShr | 2, 0xF, 0xF>(x);
       x += dpp0<kDppRowShr | 4, 0xF, 0xF>(x);
       x += dpp0<kDppRowShr | 8, 0xF, 0xF>(x);
-      x += dpp0<kDppRowBcast15, 0xA, 0xF>(x);
+      if (kWords >= 32) x += dpp0<kDppRowBcast15, 0xA, 0xF>(x);
       if (kWords == kWave) x += dpp0<kDppRowBcast31, 0xC, 0xF>(x);
       if (on) {
         s_bits[r * kRowStride + w] = m;
@@ -389,6 +389,7 @@ hipError_t launch_columns(const SpreadArgs& a, uint32_t nblocks, hipStream_t s) 
 }
 
 hipError_t launch_rows(const SpreadArgs& a, uint32_t row_items, uint32_t nblocks, hipStream_t s) {
+  if (row_items == Shape<256>::kItems) return launch<true, 256>(a, nblocks, s);
   if (row_items == Shape<512>::kItems) return launch<true, 512>(a, nblocks, s);
   if (row_items == Shape<1024>::kItems) return launch<true, 1024>(a, nblocks, s);
   return hipErrorInvalidValue;

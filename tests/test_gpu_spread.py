@@ -113,10 +113,17 @@ def test_culled(share, drop):
     check(800, 640, rec, drop_culled=drop)
 
 
-def test_uneven_batch():
+@pytest.mark.parametrize("wide", [0, 4])
+def test_uneven_batch(wide):
     """Frames of one Gaussian, none, all culled, one tile, tall and wide, in
-    one segmented sort."""
-    frames = []
+    one segmented sort; with full-HD frames beside them the columns are many
+    and thinly filled, and the row pass takes its smallest workgroups, one
+    column just past one of them."""
+    frames = [(1920, 1080, records(120, 68, 3000, 90 + i, big=0.0)) for i in range(wide)]
+    if wide:
+        one = records(1, 30, 1025, 99, big=0.0)
+        one["mean_x"], one["radius"] = 128, np.maximum(one["radius"], 1)
+        frames.append((16, 480, one))
     for i, (tx, ty, n) in enumerate([(40, 23, 9000), (1, 1, 300), (7, 2, 0), (120, 68, 20_000), (2, 80, 5000),
                                      (200, 3, 5000), (16, 16, 1), (9, 9, 2048), (30, 70, 4097)]):
         rec = records(tx, ty, n, 50 + i, big=0.02, few_depths=i % 2 == 0)
