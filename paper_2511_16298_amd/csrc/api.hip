@@ -547,8 +547,8 @@ struct PassChain {
   const uint32_t* seg_wgs;
   const uint32_t* seg_base;
   uint32_t frame_stride;
-  // the depth sort: work beside its first three passes (SideWork), or NULL
-  const SideWork* side;       // [3]
+  // the depth sort: work beside its passes (SideWork), or NULL
+  const SideWork* side;       // [npasses]
   // waits, test hook, persistent 64-bit passes (pass p's zeroed counter at
   // tickets + p; NULL: one workgroup per tile)
   uint32_t spin_limit;
@@ -624,7 +624,7 @@ ss_status run_chain(Launcher& L, uint32_t kind, const PassChain& c, hipStream_t 
                                             static_cast<int>(c.cfg.threads));
         if (narrow != 0) rb = narrow;
       }
-      if (c.side != nullptr && p < 3) {
+      if (c.side != nullptr) {
         if (launch_depth_side(a, c.side[p], static_cast<int>(c.cfg.items), static_cast<int>(c.cfg.threads), c.nblocks,
                               s) != hipSuccess)
           return SS_ERR_HIP;
@@ -1045,7 +1045,7 @@ ss_status run_spread(Launcher& L, const SpreadLayout& lay, const SpreadShape& sh
   // third the row pass's workgroups
   uint32_t* live = (o.flags & SS_FLAG_DROP_CULLED) != 0 ? scal + 4 : nullptr;
   uint32_t* pair_base = at<uint32_t>(ws, lay.pair_base);
-  SideWork side[3] = {};
+  SideWork side[4] = {};   // the last pass: none
   side[0].kind = SideWork::kPlan;
   side[0].row_items = lay.row_items;
   side[0].n_frames = lay.n_frames;

@@ -107,15 +107,15 @@ struct SpreadChunk {
 };
 static_assert(sizeof(SpreadChunk) == 16, "one 16-byte load");
 
-// Work that extra workgroups of the first three depth passes do beside the
-// pass, so that it costs no launch:
+// Work that extra workgroups of the depth passes do beside the pass, so that
+// it costs no launch:
 //   kPlan: one per frame, its plan from the span histograms and its column
 //     chunks;
 //   kTotals: one, the pair totals and the status, and the frames' first column
 //     items and row chunks;
 //   kRows: one per frame, its row chunks.
 struct SideWork {
-  enum Kind : uint32_t { kPlan = 1, kTotals = 2, kRows = 3 };
+  enum Kind : uint32_t { kNone = 0, kPlan = 1, kTotals = 2, kRows = 3 };
   uint32_t kind;
   uint32_t row_items;        // column items per workgroup of the row pass
   uint32_t n_frames;

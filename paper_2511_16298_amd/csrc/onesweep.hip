@@ -147,7 +147,7 @@ __device__ __forceinline__ void range_boundary(uint32_t* __restrict__ ranges, in
   ranges[2 * static_cast<size_t>(t)] = o;
 }
 
-template <typename K, int RB, int ITEMS, int THREADS, int MODE, bool FULL>
+template <typename K, int RB, int ITEMS, int THREADS, int MODE, bool FULL, bool TIERS>
 __device__ __forceinline__ void pass_rest(const PassArgs& a, PassSmem<K, RB, ITEMS, THREADS, MODE>& sm, uint32_t t,
                                           uint32_t base, uint32_t n, K (&k)[ITEMS], uint32_t (&v)[ITEMS],
                                           uint32_t (&dg)[ITEMS], const SegCtx& sc) {
@@ -195,8 +195,8 @@ __device__ __forceinline__ void pass_rest(const PassArgs& a, PassSmem<K, RB, ITE
       bcnt += c;
     }
     // kPassUnpack publishes after the permute, with its largest tile part
-    if (MODE != kPassUnpack)
-      st_agent(&a.lookback[static_cast<size_t>(t) * BINS + tid], (t == sc.first ? kLbInc32 : kLbAgg32) | bcnt);
+    if (MODE != kPassUnpack && (!TIERS || tier_member(t, sc.first)))
+      st_agent(&a.lookback[static_cast<size_t>(t) * BINS + tid], (!TIERS && t == sc.first ? kLbInc32 : kLbAgg32) | bcnt);
   }
   uint32_t gbase, lexcl;
   uint32_t tile_pairs = 0;  // 32-bit keys: valid items of the tile (some may be dropped)
@@ -288,6 +288,8 @@ __device__ __forceinline__ void pass_rest(const PassArgs& a, PassSmem<K, RB, ITE
     bool ok;
     if constexpr (MODE == kPassUnpack)
       ok = lookback_group<G, LbWords64>(a.lookback64, t, BINS, d, a.status, excl, excl_max, sc.first, limit);
+    else if constexpr (TIERS)
+      ok = lookback_tiers<G>(a.lookback, t, BINS, d, count, a.status, excl, sc.first, limit);
     else
       ok = lookback_group<G, LbWords32>(a.lookback, t, BINS, d, a.status, excl, excl_max, sc.first, limit);
     if (!ok) {
@@ -295,7 +297,7 @@ __device__ __forceinline__ void pass_rest(const PassArgs& a, PassSmem<K, RB, ITE
     } else if (static_cast<uint32_t>(tid) % G == 0) {
       // the group's first lane publishes the inclusive word (the chain's
       // first workgroup published its count as inclusive already)
-      if (t != sc.first) {
+      if (!TIERS && t != sc.first) {
         if constexpr (MODE == kPassUnpack) {
           const uint32_t om = own_max_of(start, count);
           st_agent(&a.lookback64[static_cast<size_t>(t) * BINS + d],
@@ -422,14 +424,14 @@ __device__ __forceinline__ void pass_rest(const PassArgs& a, PassSmem<K, RB, ITE
   }
 }
 
-template <typename K, int RB, int ITEMS, int THREADS, int MODE, bool FULL>
+template <typename K, int RB, int ITEMS, int THREADS, int MODE, bool FULL, bool TIERS>
 __device__ __forceinline__ void pass_tile(const PassArgs& a, PassSmem<K, RB, ITEMS, THREADS, MODE>& sm, uint32_t t,
                                           uint32_t base, uint32_t n, uint32_t dropped, const SegCtx& sc) {
   K k[ITEMS];
   uint32_t v[ITEMS];
   uint32_t dg[ITEMS];
   pass_load<K, RB, ITEMS, THREADS, MODE, FULL>(a, sm, base, n, dropped, sc.hist_off, k, v, dg);
-  pass_rest<K, RB, ITEMS, THREADS, MODE, FULL>(a, sm, t, base, n, k, v, dg, sc);
+  pass_rest<K, RB, ITEMS, THREADS, MODE, FULL, TIERS>(a, sm, t, base, n, k, v, dg, sc);
 }
 
 // The extra workgroup of a chain's first 64-bit pass: digit bases of
@@ -480,7 +482,7 @@ __device__ __forceinline__ void store_depth_top(const PassArgs& a, uint32_t* s2)
   }
 }
 
-template <typename K, int RB, int ITEMS, int THREADS, int MODE, bool DROP>
+template <typename K, int RB, int ITEMS, int THREADS, int MODE, bool DROP, bool TIERS>
 __device__ __forceinline__ bool onesweep_body(const PassArgs& a, PassSmem<K, RB, ITEMS, THREADS, MODE>& sm,
                                               uint32_t t);
 
@@ -615,15 +617,22 @@ __device__ __forceinline__ void side_totals(const SideWork& s, unsigned long lon
 template <int ITEMS, int THREADS, int MODE>
 constexpr uint32_t kTileOrder = MODE == kPassKV && ITEMS == 16 && THREADS == 512 ? 3 : 0;
 
+// Most workgroups for which a pass with values looks back in tiers: what 256
+// CUs hold at once of its tile's shape (0: the shape has no such form).
+template <int ITEMS, int THREADS>
+constexpr uint32_t tier_blocks() {
+  return ITEMS == 16 && THREADS == 512 ? 512 : ITEMS == 4 && THREADS == 1024 ? 256 : 0;
+}
+
 // DROP (32-bit keys, the depth sort's first pass): may drop the culled
 // Gaussians (the decision is known only after the loads).  Workgroup b is
 // tile b, or the tile the order gives it (after the publishing workgroups).
-template <typename K, int RB, int ITEMS, int THREADS, int MODE, bool DROP>
+template <typename K, int RB, int ITEMS, int THREADS, int MODE, bool DROP, bool TIERS>
 __global__ __launch_bounds__(THREADS) void k_onesweep(PassArgs a) {
   __shared__ PassSmem<K, RB, ITEMS, THREADS, MODE> sm;
   if (a.status && *a.status != SS_OK) return;
   constexpr uint32_t kOrder = kTileOrder<ITEMS, THREADS, MODE>;
-  onesweep_body<K, RB, ITEMS, THREADS, MODE, DROP>(a, sm, kOrder == 0 ? blockIdx.x : xcd_order<kOrder>(blockIdx.x));
+  onesweep_body<K, RB, ITEMS, THREADS, MODE, DROP, TIERS>(a, sm, kOrder == 0 ? blockIdx.x : xcd_order<kOrder>(blockIdx.x));
   if constexpr (sizeof(K) == 4) {
     if (a.depth_top_out != nullptr && blockIdx.x == 0) store_depth_top<THREADS>(a, sm.dstart);
   }
@@ -632,7 +641,7 @@ __global__ __launch_bounds__(THREADS) void k_onesweep(PassArgs a) {
 // A depth pass of the spread path, with side work in the workgroups from
 // side_first on.  Where that sets the status (kTotals), the pass's own
 // workgroups do not read it on entry: they must all run.
-template <int ITEMS, int THREADS, bool DROP>
+template <int ITEMS, int THREADS, bool DROP, bool TIERS>
 __global__ __launch_bounds__(THREADS) void k_depth_side(PassArgs a, SideWork side, uint32_t side_first) {
   __shared__ PassSmem<uint32_t, 8, ITEMS, THREADS, kPassKV> sm;
   if (blockIdx.x >= side_first) {
@@ -646,7 +655,7 @@ __global__ __launch_bounds__(THREADS) void k_depth_side(PassArgs a, SideWork sid
   }
   if (side.kind != SideWork::kTotals && *a.status != SS_OK) return;
   constexpr uint32_t kOrder = kTileOrder<ITEMS, THREADS, kPassKV>;
-  onesweep_body<uint32_t, 8, ITEMS, THREADS, kPassKV, DROP>(
+  onesweep_body<uint32_t, 8, ITEMS, THREADS, kPassKV, DROP, TIERS>(
       a, sm, kOrder == 0 ? blockIdx.x : xcd_order<kOrder>(blockIdx.x));
 }
 
@@ -665,14 +674,14 @@ __global__ __launch_bounds__(THREADS, ITEMS >= 16 ? 4 : 6) void k_onesweep_persi
       sm.ticket = a.status && ld_agent(a.status) != SS_OK ? 0xFFFFFFFFu : atomicAdd(a.tickets, 1u);
     __syncthreads();
     const uint32_t t = sm.ticket;
-    if (t == 0xFFFFFFFFu || !onesweep_body<K, RB, ITEMS, THREADS, MODE, false>(a, sm, t)) break;
+    if (t == 0xFFFFFFFFu || !onesweep_body<K, RB, ITEMS, THREADS, MODE, false, false>(a, sm, t)) break;
     __syncthreads();  // every thread is done with this ticket's LDS
   }
 }
 
 // Workgroup (or ticket) t.  Returns false when t lies past the pass's last
 // tile (a persistent workgroup then stops taking tickets).
-template <typename K, int RB, int ITEMS, int THREADS, int MODE, bool DROP>
+template <typename K, int RB, int ITEMS, int THREADS, int MODE, bool DROP, bool TIERS>
 __device__ __forceinline__ bool onesweep_body(const PassArgs& a, PassSmem<K, RB, ITEMS, THREADS, MODE>& sm,
                                               uint32_t t) {
   constexpr int TILE = THREADS * ITEMS;
@@ -741,9 +750,9 @@ __device__ __forceinline__ bool onesweep_body(const PassArgs& a, PassSmem<K, RB,
   if constexpr (!DROP) {
     const uint32_t dropped = sizeof(K) == 4 && a.n_total != 0 ? a.n_total - n : 0u;
     if (end - base >= static_cast<uint32_t>(TILE))
-      pass_tile<K, RB, ITEMS, THREADS, MODE, true>(a, sm, t, base, end, dropped, sc);
+      pass_tile<K, RB, ITEMS, THREADS, MODE, true, TIERS>(a, sm, t, base, end, dropped, sc);
     else
-      pass_tile<K, RB, ITEMS, THREADS, MODE, false>(a, sm, t, base, end, dropped, sc);
+      pass_tile<K, RB, ITEMS, THREADS, MODE, false, TIERS>(a, sm, t, base, end, dropped, sc);
   } else {
     // the loads go out before the drop decision (one thread's reads of the
     // culled count), which only marks the culled as not pairs
@@ -771,11 +780,11 @@ __device__ __forceinline__ bool onesweep_body(const PassArgs& a, PassSmem<K, RB,
     // the second variant fits the registers (up to 12 items per thread)
     if constexpr (ITEMS <= 12) {
       if (n - base >= static_cast<uint32_t>(TILE) && !sm.drop) {
-        pass_rest<K, RB, ITEMS, THREADS, MODE, true>(a, sm, t, base, n, k, v, dg, sc);
+        pass_rest<K, RB, ITEMS, THREADS, MODE, true, TIERS>(a, sm, t, base, n, k, v, dg, sc);
         return true;
       }
     }
-    pass_rest<K, RB, ITEMS, THREADS, MODE, false>(a, sm, t, base, n, k, v, dg, sc);
+    pass_rest<K, RB, ITEMS, THREADS, MODE, false, TIERS>(a, sm, t, base, n, k, v, dg, sc);
   }
   return true;
 }
@@ -814,22 +823,29 @@ hipError_t pass_launch(const PassArgs& a, uint32_t nblocks, hipStream_t s) {
   grid = xcd_grid<kTileOrder<ITEMS, THREADS, MODE>>(grid);
   if constexpr (sizeof(K) == 4) {
     if (a.culled != nullptr) {
-      hipLaunchKernelGGL((k_onesweep<K, RB, ITEMS, THREADS, MODE, true>), dim3(grid), dim3(THREADS), 0, s, a);
+      hipLaunchKernelGGL((k_onesweep<K, RB, ITEMS, THREADS, MODE, true, false>), dim3(grid), dim3(THREADS), 0, s, a);
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((k_onesweep<K, RB, ITEMS, THREADS, MODE, false>), dim3(grid), dim3(THREADS), 0, s, a);
+  if constexpr (MODE == kPassKV && RB == 8 && tier_blocks<ITEMS, THREADS>() != 0) {
+    if (nblocks <= tier_blocks<ITEMS, THREADS>()) {
+      hipLaunchKernelGGL((k_onesweep<K, RB, ITEMS, THREADS, MODE, false, true>), dim3(grid), dim3(THREADS), 0, s, a);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k_onesweep<K, RB, ITEMS, THREADS, MODE, false, false>), dim3(grid), dim3(THREADS), 0, s, a);
   return hipGetLastError();
 }
 
-template <int ITEMS, int THREADS>
+template <int ITEMS, int THREADS, bool TIERS>
 hipError_t depth_side_launch(const PassArgs& a, const SideWork& side, uint32_t nblocks, hipStream_t s) {
   const uint32_t first = xcd_grid<kTileOrder<ITEMS, THREADS, kPassKV>>(nblocks);
-  const uint32_t grid = first + (side.kind == SideWork::kTotals ? 1u : side.n_frames);
+  const uint32_t grid =
+      first + (side.kind == SideWork::kNone ? 0u : side.kind == SideWork::kTotals ? 1u : side.n_frames);
   if (a.culled != nullptr)
-    hipLaunchKernelGGL((k_depth_side<ITEMS, THREADS, true>), dim3(grid), dim3(THREADS), 0, s, a, side, first);
+    hipLaunchKernelGGL((k_depth_side<ITEMS, THREADS, true, TIERS>), dim3(grid), dim3(THREADS), 0, s, a, side, first);
   else
-    hipLaunchKernelGGL((k_depth_side<ITEMS, THREADS, false>), dim3(grid), dim3(THREADS), 0, s, a, side, first);
+    hipLaunchKernelGGL((k_depth_side<ITEMS, THREADS, false, TIERS>), dim3(grid), dim3(THREADS), 0, s, a, side, first);
   return hipGetLastError();
 }
 
@@ -958,8 +974,12 @@ hipError_t launch_pass(const PassArgs& a, int key_bytes, int radix_bits, int ite
 hipError_t launch_depth_side(const PassArgs& a, const SideWork& side, int items, int threads, uint32_t nblocks,
                              hipStream_t s) {
   if (a.status == nullptr || nblocks == 0) return hipErrorInvalidValue;
-  if (items == 16 && threads == 512) return depth_side_launch<16, 512>(a, side, nblocks, s);
-  if (items == 4 && threads == 1024) return depth_side_launch<4, 1024>(a, side, nblocks, s);
+#define SS_DEPTH_CASE(IT, TH)                                                             \
+  if (items == IT && threads == TH)                                                        \
+    return nblocks <= tier_blocks<IT, TH>() ? depth_side_launch<IT, TH, true>(a, side, nblocks, s) \
+                                            : depth_side_launch<IT, TH, false>(a, side, nblocks, s);
+  SS_DEPTH_CASE(16, 512) SS_DEPTH_CASE(4, 1024)
+#undef SS_DEPTH_CASE
   return hipErrorInvalidValue;
 }
 
