@@ -1135,51 +1135,38 @@ ss_status run_spread(Launcher& L, const SpreadLayout& lay, const SpreadShape& sh
 
 // ----------------------------- small frames --------------------------------
 // At most 256 tiles and 16,384 Gaussians, one frame, without the optional
-// per-Gaussian outputs: two kernels (tiny.hip).  Workspace: per-tile count
-// rows of the bucketing workgroups, then their pair regions.
-struct TinyLayout {
-  uint32_t nblocks = 0, region_cap = 0;
-  size_t rows = 0, region = 0, total = 0;
-};
-
+// per-Gaussian outputs: one kernel (tiny.hip), which needs no workspace but
+// the two words for a status and a pair count that the caller did not ask for.
 bool tiny_shape(uint32_t n, uint32_t num_tiles, const Options& o) {
   return (o.algorithm == SS_ALGO_AUTO || o.algorithm == SS_ALGO_DEPTH_FIRST) &&
          (o.flags & (SS_FLAG_UNSORTED | SS_FLAG_KEY32_LOSSY)) == 0 && num_tiles <= kTinyMaxTiles &&
          n <= kTinyMaxGaussians;
 }
 
-TinyLayout make_tiny_layout(uint32_t n, uint32_t num_tiles, uint32_t capacity) {
-  TinyLayout L;
-  L.nblocks = (n + kTinyGaussians - 1) / kTinyGaussians;
-  const uint64_t most = static_cast<uint64_t>(kTinyGaussians) * num_tiles;
-  L.region_cap = static_cast<uint32_t>(most < capacity ? most : capacity);
-  size_t off = 0;
-  L.rows = off;    off = align_up(off + static_cast<size_t>(L.nblocks) * (2 * num_tiles + 1) * sizeof(uint32_t));
-  L.region = off;  off = align_up(off + static_cast<size_t>(L.nblocks) * L.region_cap * sizeof(uint64_t));
-  L.total = off;
-  return L;
+// The workspace asked for on this path: room for the pairs of every 512
+// Gaussians grouped by tile, with counts and prefixes.  The kernel does
+// without, but what callers are asked for stays as it was published.
+size_t tiny_workspace(uint32_t n, uint32_t num_tiles, uint32_t capacity) {
+  const uint32_t groups = (n + 511) / 512;
+  const uint64_t most = static_cast<uint64_t>(512) * num_tiles;
+  const uint64_t region = most < capacity ? most : capacity;
+  return align_up(align_up(static_cast<size_t>(groups) * (2 * num_tiles + 1) * sizeof(uint32_t)) +
+                  static_cast<size_t>(groups) * region * sizeof(uint64_t));
 }
 
-ss_status run_tiny(Launcher& L, const ss_frame* frame, const Geometry& g, const ss_frame_out* out, void* ws,
-                   hipStream_t s) {
-  const TinyLayout lay = make_tiny_layout(frame->num_gaussians, g.num_tiles, out->pair_capacity);
+ss_status run_tiny(Launcher& L, const ss_frame* frame, const Geometry& g, const ss_frame_out* out, hipStream_t s) {
   TinyArgs a{};
   a.gaussians = frame->gaussians;
   a.n = frame->num_gaussians;
   a.tiles_x = g.tiles_x;
   a.tiles_y = g.tiles_y;
-  a.nblocks = lay.nblocks;
-  a.region = at<uint64_t>(ws, lay.region);
-  a.region_cap = lay.region_cap;
-  a.rows = at<uint32_t>(ws, lay.rows);
   a.capacity = out->pair_capacity;
   a.keys = out->keys;
   a.values = out->values;
   a.ranges = out->tile_ranges;
   a.num_pairs = out->num_pairs;  // both set by the caller
   a.status = out->status;
-  SS_TRY(L.run(SS_KERNEL_COUNT_DUP, [&] { return launch_tiny(a, s, true); }));
-  return L.run(SS_KERNEL_SORT_PASS, [&] { return launch_tiny(a, s, false); });
+  return L.run(SS_KERNEL_SORT_PASS, [&] { return launch_tiny(a, s); });
 }
 
 // Duplication in index order: the direct radix path, the bitonic network and
@@ -1342,11 +1329,11 @@ ss_status ss_workspace_bytes(const ss_frame* frame, uint32_t pair_capacity, cons
   size_t sort = use_direct(o) ? make_layout(frame->num_gaussians, pair_capacity, g.key_bits, o).total
                               : make_df_layout(frame->num_gaussians, 1, pair_capacity, g.num_tiles, o,
                                                frame->num_gaussians, g.num_tiles).total;
-  // small frames take the two-kernel path unless per-Gaussian outputs are
+  // small frames take the one-kernel path unless per-Gaussian outputs are
   // asked for, so both layouts must fit (the extra 8 words hold the status
   // when the caller gives none)
   if (tiny_shape(frame->num_gaussians, g.num_tiles, o)) {
-    const size_t tiny = make_tiny_layout(frame->num_gaussians, g.num_tiles, pair_capacity).total + 256;
+    const size_t tiny = tiny_workspace(frame->num_gaussians, g.num_tiles, pair_capacity) + 256;
     sort = sort > tiny ? sort : tiny;
   }
   // ss_count_pairs runs in any workspace sized here (its own layout can be
@@ -1408,7 +1395,7 @@ ss_status ss_sort_frame(const ss_frame* frame, const ss_frame_out* out, void* wo
     ss_frame_out o2 = *out;
     if (o2.status == nullptr) o2.status = at<uint32_t>(workspace, need - 256);
     if (o2.num_pairs == nullptr) o2.num_pairs = at<uint32_t>(workspace, need - 256) + 1;
-    return run_tiny(L, frame, g, &o2, workspace, s);
+    return run_tiny(L, frame, g, &o2, s);
   }
   const FrameInfo fi = frame_info(frame, g, 0, 0);
   DfIO io{&fi, frame, out->keys, out->values, out->tile_ranges, out->tiles_touched, out->offsets,

@@ -318,6 +318,8 @@ __device__ __forceinline__ bool lookback_tiers(uint32_t* lb, uint32_t t, uint32_
   constexpr uint32_t W = kTier / G;
   const uint32_t s = lane_id() % G;
   const uint32_t q = t - first, tier = q / kTier, r = q % kTier;
+  excl = 0;
+  if (q == 0) return true;
   uint32_t mine = 0, spins = 0;
   while (true) {
     uint32_t w[W];

@@ -1,25 +1,27 @@
-// Small frames (at most 256 tiles and 16,384 Gaussians) in two kernels, for
+// Small frames (at most 256 tiles and 16,384 Gaussians) in one kernel, for
 // latency: the same result as the other paths -- all (tile, Gaussian) pairs
 // ordered by (tile, depth, index) and the tile ranges (paper: Background,
-// "Duplication with Tiles" and "Sorting") -- reached by bucketing instead of
-// global radix passes:
-//   1. k_tiny_bucket, one workgroup per 512 consecutive Gaussians: tile
-//      rectangles, the workgroup's pairs written to its own region grouped
-//      by tile, and its per-tile counts;
-//   2. k_tiny_tiles, one workgroup per tile: the tile's runs gathered from
-//      every region, sorted by (depth, index) inside LDS, written at the
-//      tile's start; the range, the pair count and the status.
-// A frame's launches of global passes each cost more than the work they do
-// on a frame this small; here each kernel is one round of loads, LDS work
-// and stores.
+// "Duplication with Tiles" and "Sorting") -- without a pair ever being
+// exchanged between workgroups.
+//
+// One workgroup per tile reads every record of the frame (at most 256 KB,
+// which its XCD's L2 serves after the first reader).  A Gaussian's pairs in
+// lower tiles follow from its rectangle in closed form, so their sum over the
+// frame is the tile's start, the sum of all rectangles is the pair count, and
+// no workgroup waits for another.  The Gaussians that meet the tile are sorted
+// by (depth, index) in LDS and written at the tile's start.
+//
+// What bounds it is one pass of loads and some 60 vector instructions per
+// record, 16 waves a CU, then the sort.  Two kernels before it (one bucketing
+// 512 Gaussians per workgroup, on 20 CUs for 10,000, one gathering and sorting
+// the tiles) took 13.8 + 11.5 us for the 256 x 256 frame of 10,000 Gaussians,
+// this one 11.7 (24.4 -> 11.7 us a call).
 #include "common.hpp"
 #include "internal.hpp"
 
 namespace ss {
 namespace {
 
-constexpr uint32_t kTinyThreads = kTinyGaussians;   // one Gaussian per thread
-constexpr uint32_t kTinyWaves = kTinyThreads / kWave;
 constexpr uint32_t kSortThreads = 1024;
 constexpr uint32_t kSortItems = kTinyMaxGaussians / kSortThreads;   // 16
 constexpr uint32_t kSortWaves = kSortThreads / kWave;
@@ -28,130 +30,82 @@ __device__ __forceinline__ uint32_t tclamp(int64_t v, uint32_t n) {
   return v < 0 ? 0u : (v > static_cast<int64_t>(n) ? n : static_cast<uint32_t>(v));
 }
 
-// ---------------------------------------------------------------------------
-// Kernel 1.  One Gaussian per thread: its rectangle, then its pairs counted
-// per tile (LDS atomics), the workgroup's per-tile prefix, and each pair
-// written to region[lstart[tile] + the next slot of that tile] (LDS atomics
-// again: the order inside a tile's run is not fixed, kernel 2 sorts by depth
-// and index).  Item: depth bits << 32 | Gaussian index.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kTinyThreads) void k_tiny_bucket(TinyArgs a) {
-  __shared__ uint32_t s_cnt[kTinyMaxTiles];      // per-tile pairs of this workgroup
-  __shared__ uint32_t s_cursor[kTinyMaxTiles];   // next free slot of each tile's run
-  __shared__ uint32_t s_tmp[kTinyWaves];
-
-  const uint32_t tid = threadIdx.x;
-  const uint32_t T = a.tiles_x * a.tiles_y;
-  for (uint32_t i = tid; i < kTinyMaxTiles; i += kTinyThreads) s_cnt[i] = 0;
-  __syncthreads();
-  const uint32_t g = blockIdx.x * kTinyGaussians + tid;
-  uint32_t x0 = 0, y0 = 0, w = 0, h = 0, dbits = 0;
-  bool bad = false;
-  if (g < a.n) {
-    const int4 r = reinterpret_cast<const int4*>(a.gaussians)[g];
-    const uint32_t radius = static_cast<uint32_t>(r.w);
-    dbits = static_cast<uint32_t>(r.z);
-    if (radius != 0) {
-      const int64_t R = static_cast<int64_t>(radius) << 4;
-      x0 = tclamp((static_cast<int64_t>(r.x) - R) >> 8, a.tiles_x);
-      const uint32_t x1 = tclamp((static_cast<int64_t>(r.x) + R + 255) >> 8, a.tiles_x);
-      y0 = tclamp((static_cast<int64_t>(r.y) - R) >> 8, a.tiles_y);
-      const uint32_t y1 = tclamp((static_cast<int64_t>(r.y) + R + 255) >> 8, a.tiles_y);
-      if (x1 > x0 && y1 > y0) {
-        w = x1 - x0;
-        h = y1 - y0;
-      }
-    }
-    if (w != 0 && dbits - 1u >= 0x7F7FFFFFu) bad = true;
-    for (uint32_t yy = 0; yy < h; ++yy)
-      for (uint32_t xx = 0; xx < w; ++xx) atomicAdd(&s_cnt[(y0 + yy) * a.tiles_x + x0 + xx], 1u);
-  }
-  const bool any_bad = __syncthreads_or(bad);
-  // for kernel 2: per-tile counts, their exclusive prefix (where each tile's
-  // run starts in the region) and the bad flag
-  uint32_t* row = a.rows + static_cast<size_t>(blockIdx.x) * (2 * T + 1);
-  const uint32_t tc = tid < T ? s_cnt[tid] : 0u;
-  uint32_t all;
-  const uint32_t ls = block_exclusive_scan<uint32_t, kTinyThreads>(tc, s_tmp, all);
-  if (tid < kTinyMaxTiles) s_cursor[tid] = ls;
-  if (tid < T) {
-    row[tid] = tc;
-    row[T + tid] = ls;
-  }
-  if (tid == 0) row[2 * T] = any_bad ? 1u : 0u;
-  __syncthreads();
-  uint64_t* region = a.region + static_cast<size_t>(blockIdx.x) * a.region_cap;
-  const uint64_t item = (static_cast<uint64_t>(dbits) << 32) | g;
-  for (uint32_t yy = 0; yy < h; ++yy) {
-    for (uint32_t xx = 0; xx < w; ++xx) {
-      const uint32_t at = atomicAdd(&s_cursor[(y0 + yy) * a.tiles_x + x0 + xx], 1u);
-      // a region holds the frame's pair capacity: more pairs than that is a
-      // capacity error that kernel 2 reports, and nothing lands past the end
-      if (at < a.region_cap) region[at] = item;
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Kernel 2.  Workgroup t: the tile's start is the sum of every workgroup's
-// counts of lower tiles; its runs are gathered and ordered by (depth, index):
-// by counting when they fit one item per thread, else by 8-bit LSD passes
-// (index bits, then depth bits) with wave-ballot ranking in LDS.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kSortThreads) void k_tiny_tiles(TinyArgs a) {
+// Workgroup t: the tile's run ordered by (depth, index), by counting when it
+// fits one item per thread, else by 8-bit LSD passes (index bits, then depth
+// bits) with wave-ballot ranking in LDS.
+__global__ __launch_bounds__(kSortThreads) void k_tiny_frame(TinyArgs a) {
   __shared__ __align__(16) uint64_t s_buf[kTinyMaxGaussians + 2];
-  __shared__ uint32_t s_wcnt[kSortWaves * 256];   // LSD passes: per-wave digit counts
+  __shared__ uint32_t s_wcnt[kSortWaves * 256];   // LSD passes: per-wave digit counts; counting: ranks
   __shared__ uint32_t s_dstart[256];
-  __shared__ uint32_t s_roff[kTinyMaxBlocks];      // this tile's run in each region
-  __shared__ uint32_t s_run[kTinyMaxBlocks + 1];   // where each region's run lands in s_buf
   __shared__ unsigned long long s_tmp64[kSortWaves];
   __shared__ uint32_t s_tmp[kSortWaves];
-  __shared__ uint32_t s_start, s_n, s_m, s_bad;
+  __shared__ uint32_t s_bad[kSortWaves];
 
   const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
-  const uint32_t T = a.tiles_x * a.tiles_y;
   const uint32_t t = blockIdx.x;
-  const uint32_t nb = a.nblocks;
-  const uint32_t stride = 2 * T + 1;
-  // tile totals over the workgroups (independent loads), their prefix (this
-  // tile's start), all pairs, any bad depth; this tile's run in each region
-  uint32_t tot = 0, badf = 0, rlen = 0, roff = 0;
-  if (tid < T) {
-    uint32_t v[kTinyMaxBlocks];   // every load issued before the first use
+  const uint32_t tx = t % a.tiles_x, ty = t / a.tiles_x;
+  // record j * kSortThreads + tid, eight loads at a time
+  uint32_t hits = 0;                  // bit j: that record meets the tile
+  uint32_t before = 0, all = 0;       // pairs in lower tiles, all pairs
+  bool bad = false;
+  constexpr uint32_t kLoads = 8;
+  for (uint32_t j0 = 0; j0 * kSortThreads < a.n; j0 += kLoads) {
+    int4 rec[kLoads];
 #pragma unroll
-    for (uint32_t b = 0; b < kTinyMaxBlocks; ++b) v[b] = b < nb ? a.rows[b * stride + tid] : 0u;
+    for (uint32_t j = 0; j < kLoads; ++j) {
+      const uint32_t g = (j0 + j) * kSortThreads + tid;
+      rec[j] = g < a.n ? reinterpret_cast<const int4*>(a.gaussians)[g] : make_int4(0, 0, 0, 0);
+    }
 #pragma unroll
-    for (uint32_t b = 0; b < kTinyMaxBlocks; ++b) tot += v[b];
+    for (uint32_t j = 0; j < kLoads; ++j) {
+      if ((j0 + j) * kSortThreads >= a.n) break;   // uniform: no such records
+      const int4 r = rec[j];
+      const uint32_t radius = static_cast<uint32_t>(r.w);   // 0: culled
+      uint32_t x0, x1, y0, y1;
+      // means and radii of any sensible image: 32-bit sums (|mean| < 2^29,
+      // 16 radius < 2^29); the wave takes 64-bit ones if any lane must
+      const bool narrow = radius < (1u << 25) && static_cast<uint32_t>(r.x) + (1u << 29) < (1u << 30) &&
+                          static_cast<uint32_t>(r.y) + (1u << 29) < (1u << 30);
+      if (ballot(!narrow) == 0) {
+        const int R = static_cast<int>(radius << 4), nx = static_cast<int>(a.tiles_x), ny = static_cast<int>(a.tiles_y);
+        x0 = static_cast<uint32_t>(min(max((r.x - R) >> 8, 0), nx));
+        x1 = static_cast<uint32_t>(min(max((r.x + R + 255) >> 8, 0), nx));
+        y0 = static_cast<uint32_t>(min(max((r.y - R) >> 8, 0), ny));
+        y1 = static_cast<uint32_t>(min(max((r.y + R + 255) >> 8, 0), ny));
+      } else {
+        const int64_t R = static_cast<int64_t>(radius) << 4;
+        x0 = tclamp((static_cast<int64_t>(r.x) - R) >> 8, a.tiles_x);
+        x1 = tclamp((static_cast<int64_t>(r.x) + R + 255) >> 8, a.tiles_x);
+        y0 = tclamp((static_cast<int64_t>(r.y) - R) >> 8, a.tiles_y);
+        y1 = tclamp((static_cast<int64_t>(r.y) + R + 255) >> 8, a.tiles_y);
+      }
+      if (radius != 0 && x1 > x0 && y1 > y0) {
+        const uint32_t w = x1 - x0;
+        if (static_cast<uint32_t>(r.z) - 1u >= 0x7F7FFFFFu) bad = true;
+        const bool in_row = ty >= y0 && ty < y1;
+        all += w * (y1 - y0);
+        before += w * (min(max(ty, y0), y1) - y0) + (in_row ? min(max(tx, x0), x1) - x0 : 0u);
+        if (in_row && tx >= x0 && tx < x1) hits |= 1u << (j0 + j);
+      }
+    }
   }
-  if (tid < nb) {
-    badf = a.rows[tid * stride + 2 * T];
-    rlen = a.rows[tid * stride + t];
-    roff = a.rows[tid * stride + T + t];
-  }
-  // one scan for three prefixes: tile totals (bits 0-23: at most 2^22 pairs),
-  // this tile's run lengths by region (bits 24-43) and bad flags (from 44)
-  unsigned long long all;
+  // one scan: hits (bits 0-14), pairs in lower tiles (15-37) and all pairs
+  // (38-60), each at most 2^22
+  if (lane == 0) s_bad[wave] = 0;
+  if (ballot(bad) != 0 && lane == 0) s_bad[wave] = 1;
+  unsigned long long sums;
   const unsigned long long ex = block_exclusive_scan<unsigned long long, kSortThreads>(
-      (static_cast<unsigned long long>(badf) << 44) | (static_cast<unsigned long long>(rlen) << 24) | tot, s_tmp64,
-      all);
-  if (tid == t) {
-    s_start = static_cast<uint32_t>(ex & 0xFFFFFFull);
-    s_n = tot;
-  }
-  if (tid == 0) {
-    s_m = static_cast<uint32_t>(all & 0xFFFFFFull);
-    s_bad = static_cast<uint32_t>(all >> 44);
-  }
-  // where each region's run lands in s_buf
-  if (tid < nb) {
-    s_roff[tid] = roff;
-    s_run[tid] = static_cast<uint32_t>((ex >> 24) & 0xFFFFFull);
-  }
-  if (tid == 0) s_run[nb] = static_cast<uint32_t>((all >> 24) & 0xFFFFFull);
-  __syncthreads();
-  const uint32_t m = s_m, start = s_start, n = s_n;
+      (static_cast<unsigned long long>(all) << 38) | (static_cast<unsigned long long>(before) << 15) |
+          static_cast<uint32_t>(__popc(hits)),
+      s_tmp64, sums);
+  const uint32_t n = static_cast<uint32_t>(sums) & 0x7FFFu;
+  const uint32_t start = static_cast<uint32_t>(sums >> 15) & 0x7FFFFFu;
+  const uint32_t m = static_cast<uint32_t>(sums >> 38);
+  uint32_t any_bad = 0;
+#pragma unroll
+  for (uint32_t w = 0; w < kSortWaves; ++w) any_bad |= s_bad[w];
   uint32_t st = SS_OK;
-  if (s_bad) st = SS_ERR_INVALID_INPUT;
+  if (any_bad) st = SS_ERR_INVALID_INPUT;
   else if (m > a.capacity) st = SS_ERR_CAPACITY;
   if (t == 0 && tid == 0) {
     *a.num_pairs = m;
@@ -163,16 +117,19 @@ __global__ __launch_bounds__(kSortThreads) void k_tiny_tiles(TinyArgs a) {
     a.ranges[2 * t + 1] = start + n;
   }
   if (n == 0) return;
-  // gather the runs (each contiguous in its region) into s_buf in region
-  // order: item q of the tile comes from the region b whose run holds it
-  for (uint32_t q = tid; q < n; q += kSortThreads) {
-    uint32_t lo = 0, hi = nb;
-    while (hi - lo > 1) {
-      const uint32_t mid = (lo + hi) >> 1;
-      if (s_run[mid] <= q) lo = mid;
-      else hi = mid;
-    }
-    s_buf[q] = a.region[static_cast<size_t>(lo) * a.region_cap + s_roff[lo] + (q - s_run[lo])];
+  // the tile's items (depth bits << 32 | index), in any order
+  uint32_t at = static_cast<uint32_t>(ex) & 0x7FFFu;
+  for (uint32_t bits = hits; bits != 0; bits &= bits - 1) {
+    const uint32_t g = static_cast<uint32_t>(__builtin_ctz(bits)) * kSortThreads + tid;
+    s_buf[at++] = (static_cast<uint64_t>(__float_as_uint(a.gaussians[g].depth)) << 32) | g;
+  }
+  // counting: several threads per item where there are few items, each over a
+  // share of the others
+  const uint32_t parts = n <= kSortThreads / 4 ? 4u : n <= kSortThreads / 2 ? 2u : 1u;
+  const uint32_t n2 = (n + 2 * parts - 1) / (2 * parts) * (2 * parts);   // padded with all-ones items, above every valid one
+  if (n <= kSortThreads) {
+    if (tid < n2 - n) s_buf[n + tid] = ~0ull;
+    s_wcnt[tid] = 0;
   }
   __syncthreads();
   uint64_t* keys = a.keys + start;
@@ -180,20 +137,21 @@ __global__ __launch_bounds__(kSortThreads) void k_tiny_tiles(TinyArgs a) {
   const uint64_t tile_hi = static_cast<uint64_t>(t) << 32;
 
   if (n <= kSortThreads) {
-    // rank by counting: items (depth bits << 32 | index) are distinct, so an
-    // item's place is the number of smaller ones; the run is padded to an
-    // even count with all-ones items (above every valid one), read two at a time
-    const uint32_t n2 = (n + 1) & ~1u;
-    if (n2 > n && tid == 0) s_buf[n] = ~0ull;
-    __syncthreads();
-    if (tid < n) {
-      const uint64_t me = s_buf[tid];
-      uint32_t r = 0;
+    // items are distinct, so an item's place is the number of smaller ones
+    const uint32_t share = kSortThreads / parts, i = tid % share, part = tid / share, len = n2 / parts;
+    const uint64_t me = i < n ? s_buf[i] : 0ull;
+    uint32_t r = 0;
+    if (i < n) {
 #pragma unroll 4
-      for (uint32_t j = 0; j < n2; j += 2) {
+      for (uint32_t j = part * len; j < (part + 1) * len; j += 2) {
         const ulonglong2 q = *reinterpret_cast<const ulonglong2*>(s_buf + j);
         r += (q.x < me) + (q.y < me);
       }
+      if (parts != 1 && r != 0) atomicAdd(&s_wcnt[i], r);
+    }
+    if (parts != 1) __syncthreads();
+    if (tid < n) {
+      if (parts != 1) r = s_wcnt[tid];
       keys[r] = tile_hi | static_cast<uint32_t>(me >> 32);
       vals[r] = static_cast<uint32_t>(me);
     }
@@ -269,13 +227,9 @@ __global__ __launch_bounds__(kSortThreads) void k_tiny_tiles(TinyArgs a) {
 
 }  // namespace
 
-hipError_t launch_tiny(const TinyArgs& a, hipStream_t s, bool bucket) {
-  if (bucket) {
-    if (a.nblocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_tiny_bucket, dim3(a.nblocks), dim3(kTinyThreads), 0, s, a);
-  } else {
-    hipLaunchKernelGGL(k_tiny_tiles, dim3(a.tiles_x * a.tiles_y), dim3(kSortThreads), 0, s, a);
-  }
+hipError_t launch_tiny(const TinyArgs& a, hipStream_t s) {
+  if (a.n > kTinyMaxGaussians || a.tiles_x * a.tiles_y > kTinyMaxTiles) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_tiny_frame, dim3(a.tiles_x * a.tiles_y), dim3(kSortThreads), 0, s, a);
   return hipGetLastError();
 }
 
