@@ -621,7 +621,7 @@ constexpr uint32_t kTileOrder = MODE == kPassKV && ITEMS == 16 && THREADS == 512
 // CUs hold at once of its tile's shape (0: the shape has no such form).
 template <int ITEMS, int THREADS>
 constexpr uint32_t tier_blocks() {
-  return ITEMS == 16 && THREADS == 512 ? 512 : ITEMS == 4 && THREADS == 1024 ? 256 : 0;
+  return (ITEMS == 16 || ITEMS == 8) && THREADS == 512 ? 512 : ITEMS == 4 && THREADS == 1024 ? 256 : 0;
 }
 
 // DROP (32-bit keys, the depth sort's first pass): may drop the culled

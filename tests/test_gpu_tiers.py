@@ -12,15 +12,18 @@ import synth  # noqa: E402
 
 
 @pytest.mark.parametrize("workgroups", [1, 15, 16, 17, 31, 32, 33, 48, 511, 512, 513])
+@pytest.mark.parametrize("items", [8, 16])
 @pytest.mark.parametrize("extra", [0, 1])
-def test_pairs(workgroups, extra):
-    """Key + value passes of 8,192-pair workgroups; few distinct keys, so that
-    stability shows."""
-    n = 8192 * workgroups - (1 - extra) * 5
+def test_pairs(workgroups, items, extra):
+    """Key + value passes of 4,096- and 8,192-pair workgroups, asked for and
+    (on both sides of 1.25M pairs) taken by default; few distinct keys, so
+    that stability shows."""
+    n = 512 * items * workgroups - (1 - extra) * 5
     print(f"{workgroups} workgroups, n={n}", flush=True)
     rs = np.random.default_rng(n)
     keys = rs.integers(0, 1 << 45, 97, dtype=np.int64)[rs.integers(0, 97, n)]
-    k, v = ss.sort_pairs(torch.from_numpy(keys).cuda(), torch.arange(n, dtype=torch.int32, device="cuda"), 45)
+    k, v = ss.sort_pairs(torch.from_numpy(keys).cuda(), torch.arange(n, dtype=torch.int32, device="cuda"), 45,
+                         items_per_thread=items if extra else 0)
     order = np.argsort(keys, kind="stable")
     assert np.array_equal(v.cpu().numpy(), order.astype(np.int32))
     assert np.array_equal(k.cpu().numpy(), keys[order])
