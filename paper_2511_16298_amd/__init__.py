@@ -357,38 +357,45 @@ class Server:
             pass
 
 
-def count_pairs(records, width: int, height: int, stream=None):
-    """Counting and scan: (tiles_touched, offsets, num_pairs, status) device tensors."""
+def _count(records, width: int, height: int, stream, per_gaussian: bool):
+    """Counting on ``stream``: (tiles_touched, offsets) device tensors (None
+    unless ``per_gaussian``) and one device tensor of num_pairs and status."""
     torch = _torch()
     dev = records.device
     f = _frame(records, width, height)
     n = max(int(records.shape[0]), 1)
-    probe = f
-    st, ws = _abi.ss_workspace_bytes(probe, 0, None)
+    st, ws = _abi.ss_workspace_bytes(f, 0, None)
     check(st, "ss_workspace_bytes")
     with _allocating_on(stream):
         work = torch.empty(max(ws, 256), dtype=torch.uint8, device=dev)
-        tt = torch.empty(n, dtype=torch.int32, device=dev)
-        off = torch.empty(n, dtype=torch.int32, device=dev)
-        m = torch.zeros(1, dtype=torch.int32, device=dev)
-        s = torch.zeros(1, dtype=torch.int32, device=dev)
-    st = _abi.ss_count_pairs(f, tt.data_ptr(), off.data_ptr(), m.data_ptr(), s.data_ptr(),
-                             work.data_ptr(), ws, _stream_handle(stream))
+        tt = torch.empty(n, dtype=torch.int32, device=dev) if per_gaussian else None
+        off = torch.empty(n, dtype=torch.int32, device=dev) if per_gaussian else None
+        ms = torch.zeros(2, dtype=torch.int32, device=dev)
+    st = _abi.ss_count_pairs(f, tt.data_ptr() if per_gaussian else None, off.data_ptr() if per_gaussian else None,
+                             ms.data_ptr(), ms.data_ptr() + 4, work.data_ptr(), ws, _stream_handle(stream))
     check(st, "ss_count_pairs")
-    return tt, off, m, s
+    return tt, off, ms
+
+
+def count_pairs(records, width: int, height: int, stream=None):
+    """Counting and scan: (tiles_touched, offsets, num_pairs, status) device tensors."""
+    tt, off, ms = _count(records, width, height, stream, True)
+    return tt, off, ms[:1], ms[1:]
 
 
 def sort_frame(records, width: int, height: int, capacity: Optional[int] = None, stream=None,
                radix_bits: int = 0, items_per_thread: int = 0, stages: bool = False):
     """Whole frame.  With ``capacity=None`` a first call counts the pairs and
-    one 4-byte read-back sizes the buffers exactly.  Returns the sorter's
-    FrameOutput (slice ``[:M]`` after ``result()``)."""
+    one 8-byte read-back (the pair count and the status) sizes the buffers
+    exactly.  Returns the sorter's FrameOutput (slice ``[:M]`` after
+    ``result()``)."""
     if capacity is None:
-        _, _, m, s = count_pairs(records, width, height, stream)
-        st = int(s.item())
+        _, _, ms = _count(records, width, height, stream, False)
+        with _allocating_on(stream):
+            m, st = ms.tolist()
         if st != SS_OK:
             raise SplatSortError(st, "ss_count_pairs")
-        capacity = int(m.item()) & 0xFFFFFFFF
+        capacity = m & 0xFFFFFFFF
     sorter = FrameSorter(width, height, int(records.shape[0]), capacity, radix_bits, items_per_thread,
                          stages, device=records.device)
     return sorter(records, stream)
