@@ -57,7 +57,7 @@ namespace ss {
 namespace {
 
 constexpr uint32_t kMaxDigits = 256;
-constexpr uint32_t kInline = 3;
+constexpr uint32_t kInline = 2;
 
 // A workgroup of THREADS threads takes kItems = 4 * THREADS items.
 template <uint32_t THREADS>
