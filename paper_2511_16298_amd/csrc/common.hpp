@@ -221,12 +221,11 @@ struct LbWords64 {
   __device__ static uint32_t maximum(W w) { return static_cast<uint32_t>((w >> 30) & kLbMaxW); }
 };
 
-template <int G, typename P>
+template <int G, typename P, int W = kLookbackWindow>
 __device__ __forceinline__ bool lookback_group(typename P::W* lb, uint32_t t, uint32_t stride, uint32_t d,
                                                uint32_t* status, uint32_t& excl, uint32_t& excl_max,
                                                uint32_t first, uint32_t spin_limit) {
   static_assert(G >= 1 && G <= kWave && kWave % G == 0, "a group lies inside one wave");
-  constexpr int W = kLookbackWindow;
   const uint32_t lane = lane_id();
   const uint32_t s = lane % G;
   const uint32_t base = lane - s;

@@ -257,10 +257,13 @@ __device__ __forceinline__ void pass_rest(const PassArgs& a, PassSmem<K, RB, ITE
 
   // ---- decoupled look-back: pairs of digit d in earlier workgroups ----
   // G consecutive lanes per digit: two where the workgroup has the threads
-  // (16 predecessors per round), except in 16-item passes over pairs, whose
-  // long chains of tiles measured faster with one; more lanes spread each
-  // load over more rows of the look-back words and measured slower
-  constexpr int G = sizeof(K) == 8 && ITEMS >= 16 ? 1 : THREADS / BINS > 2 ? 2 : THREADS / BINS;
+  // (16 predecessors per round), except in 16-item passes, whose long chains
+  // of tiles measured faster with one; more lanes spread each load over more
+  // rows of the look-back words and measured slower.  16-item passes with
+  // values read four predecessors a round, others eight (one lane and four:
+  // 64-frame batch 2,283 -> 2,252 us, 17M pairs 682 -> 672)
+  constexpr int G = ITEMS >= 16 ? 1 : THREADS / BINS > 2 ? 2 : THREADS / BINS;
+  constexpr int W = MODE == kPassKV && ITEMS >= 16 ? 4 : kLookbackWindow;
   static_assert(G >= 1 && THREADS % BINS == 0, "whole lane groups per digit");
   if (tid < BINS * G) {
     const uint32_t d = static_cast<uint32_t>(tid) / G;
@@ -291,7 +294,7 @@ __device__ __forceinline__ void pass_rest(const PassArgs& a, PassSmem<K, RB, ITE
     else if constexpr (TIERS)
       ok = lookback_tiers<G>(a.lookback, t, BINS, d, count, a.status, excl, sc.first, limit);
     else
-      ok = lookback_group<G, LbWords32>(a.lookback, t, BINS, d, a.status, excl, excl_max, sc.first, limit);
+      ok = lookback_group<G, LbWords32, W>(a.lookback, t, BINS, d, a.status, excl, excl_max, sc.first, limit);
     if (!ok) {
       sm.timeout = 1;
     } else if (static_cast<uint32_t>(tid) % G == 0) {
