@@ -39,10 +39,10 @@ import synth  # noqa: E402
 
 PEAK_HBM_GBS = 8000.0   # MI355X HBM3E, published
 DEFAULT_WORKLOAD = "large-6m"
-PASS_SOURCE = os.path.join(ROOT, "paper_2511_16298_amd", "csrc", "onesweep.hip")
+PASS_SOURCE = os.path.join(ROOT, "paper_2511_16298_amd", "csrc", "spread.hip")
 API_SOURCE = os.path.join(ROOT, "paper_2511_16298_amd", "csrc", "api.hip")
 PROFILES = os.path.join(ROOT, "profiles")
-PASS_KERNEL = "k_onesweep"
+PASS_KERNEL = "k_spread"
 
 
 def parse():
@@ -103,12 +103,12 @@ def source_hash(paths=None) -> str:
 def dominant_kernel(workload: str):
     """(kernel-name prefix, name filter, source file) of the kernel a
     workload's roofline is quoted on: the projection kernel for the
-    preprocessing workload, else the 64-bit-key (tile) sort pass."""
+    preprocessing workload, else the row pass, which writes the sorted pairs."""
     if workload == "preprocess":
         return "k_preprocess", "", os.path.join(ROOT, "paper_2511_16298_amd", "csrc", "preprocess.hip")
     if workload == "render":
         return "k_render", "", os.path.join(ROOT, "paper_2511_16298_amd", "csrc", "render.hip")
-    return PASS_KERNEL, "unsigned long", (PASS_SOURCE, API_SOURCE)
+    return PASS_KERNEL, "<true", (PASS_SOURCE, API_SOURCE)
 
 
 def _rows(pattern: str):
@@ -158,8 +158,8 @@ def summarize_profiles(d: str, workload: str, copy_mib: int = 512,
     f_scale, w_scale = kib / (sum(fc) / len(fc)), kib / (sum(wc) / len(wc))
     # the measured kernel
     kname, kfilter, ksrc = dominant_kernel(workload)
-    # every instantiation of it (the tile passes: 8-bit, and a narrower last
-    # pass), averaged per launch like the benchmark's timing of the group
+    # every instantiation of it, averaged per launch like the benchmark's
+    # timing of the group
     tile = sorted(k for k in fby if k.startswith(kname) and kfilter in k)
     assert tile, kname
     fp = [v for k in tile for v in fby[k]]
@@ -170,7 +170,7 @@ def summarize_profiles(d: str, workload: str, copy_mib: int = 512,
     # (launches per frame = its calls / the calls of the per-frame count
     # kernel in the timing run), its measured bytes and its time
     calls = {short_name(r["Name"]): (int(r["Calls"]), float(r["AverageNs"])) for r in stats}
-    per_frame = calls.get("k_count_keys", (0, 0.0))[0]
+    per_frame = max((c for k, (c, _) in calls.items() if k.startswith("k_count_keys")), default=0)
     step = None
     if per_frame and workload != "preprocess":
         b = t_ns = 0.0
@@ -782,8 +782,33 @@ def packed_pairs(n: int, max_frame_n: int, tile_bits: int, tile_passes: int) -> 
     return tile_passes >= 1 and tile_bits <= 32 and idx_bits < 32 and field >= 27 and pos_bits <= field
 
 
+def column_items(rec, tiles_x: int, tiles_y: int) -> int:
+    """Items between the column and the row pass: over all Gaussians with
+    pairs, the tile columns that each one meets."""
+    x, y = rec["mean_x"].astype(np.int64), rec["mean_y"].astype(np.int64)
+    r = rec["radius"].astype(np.int64) * 16
+    w = np.clip((x + r + 255) >> 8, 0, tiles_x) - np.clip((x - r) >> 8, 0, tiles_x)
+    h = np.clip((y + r + 255) >> 8, 0, tiles_y) - np.clip((y - r) >> 8, 0, tiles_y)
+    return int(w[(r > 0) & (w > 0) & (h > 0)].sum())
+
+
+def spread_passes(args, tiles_x: int, tiles_y: int) -> bool:
+    """Whether the benchmark's arguments take the column and row passes (the
+    default shape, at most 256 tiles per axis)."""
+    return (args.algorithm == "depth-first" and args.radix_bits in (0, 8) and args.items in (0, 16)
+            and args.wg in (0, 512) and tiles_x <= 256 and tiles_y <= 256)
+
+
+def spread_step_bytes(n: int, m: int, c: int, tiles_x: int, tiles_y: int) -> float:
+    """Step bytes with the spread passes: count 16N read + 12N write, four
+    depth passes 24N each, column pass 12N read + 10C write (C column items),
+    row pass 10C read + 12M write + 8T."""
+    return 136.0 * n + 20.0 * c + 12.0 * m + 8.0 * tiles_x * tiles_y
+
+
 def step_bytes_model(n: int, m: int, tiles_x: int, tiles_y: int, key_bits: int, rb: int = 8) -> tuple:
-    """(depth-first step bytes, direct-path bytes, tile passes, packed) of one frame.
+    """(depth-first step bytes, direct-path bytes, tile passes, packed) of one
+    frame in the digit passes.
 
     Depth-first, frames of at most 256 tiles per axis: count 16N read + 12N
     write (packed rectangle, depth key, index), four depth passes 24N each
@@ -999,7 +1024,15 @@ def main():
     pass_bytes = 24.0 * M                       # read + write of (u64 key, u32 value) per pair
     achieved = pass_bytes / (pass_us * 1e-6) / 1e9
     step_bytes, direct_bytes, tile_passes, packed = step_bytes_model(N, M, tx, ty, key_bits, rb)
-    if (packed and args.algorithm == "depth-first" and args.radix_bits in (0, 8) and args.items in (0, 8, 16)
+    spread = spread_passes(args, tx, ty)
+    items = column_items(rec, tx, ty) if spread else 0
+    if spread:
+        # the row pass: 10-byte column items in, 12-byte pairs and ranges out
+        step_bytes = spread_step_bytes(N, M, items, tx, ty)
+        pass_bytes = 10.0 * items + 12.0 * M + 8.0 * tx * ty
+        achieved = pass_bytes / (pass_us * 1e-6) / 1e9
+        tile_passes, packed = 2, False
+    elif (packed and args.algorithm == "depth-first" and args.radix_bits in (0, 8) and args.items in (0, 8, 16)
             and args.wg in (0, 512)):
         # packed pairs: the first Pt - 1 passes move 8-byte items (16 B per
         # pair), the last reads 8 and writes 12; per launch on average
@@ -1026,10 +1059,12 @@ def main():
                                f"({tx}x{ty}={tx * ty}), N={N} projected Gaussians, seed {seed}",
                    "num_pairs": M, "key_bits": key_bits, "radix_bits": rb, "path": args.algorithm,
                    "depth_passes": kern.get("depth_pass", {}).get("launches", 0) // K,
-                   "tile_passes": tile_passes, "packed_pairs": packed, "parallelism": "single GPU"},
+                   "tile_passes": tile_passes, "packed_pairs": packed, "spread_passes": spread,
+                   "column_items": items, "parallelism": "single GPU"},
         "latency_ms": {"p50": p50, "p99": pct(step_ms, 99), "max": max(step_ms)},
-        # the dominant kernel of the step: the 64-bit-key (tile) sort pass
-        "roofline": {"bound": "hbm", "kernel": "sort_pass", "achieved": achieved, "peak": PEAK_HBM_GBS,
+        # the dominant kernel of the step: the row pass (digit passes: the
+        # 64-bit-key tile pass)
+        "roofline": {"bound": "hbm", "kernel": "row_pass" if spread else "sort_pass", "achieved": achieved, "peak": PEAK_HBM_GBS,
                      "unit": "GB/s", "frac": achieved / PEAK_HBM_GBS, "traffic": profiled_traffic(args.workload),
                      "bytes_per_launch": pass_bytes, "avg_launch_us": pass_us},
         # the whole step: the running path's algorithmic bytes over the p50
@@ -1121,8 +1156,10 @@ def main():
         for wl in ("fullhd-1m", "small-256x256"):
             steps = max(K, 200)
             o = time_frame(args, wl, steps, max(args.warmup, 20), dev, stream, kernel_timer=False)
-            sb, _, _, _ = step_bytes_model(len(o["rec"]), o["M"], o["sorter"].tiles_x, o["sorter"].tiles_y,
-                                           o["sorter"].key_bits)
+            otx, oty = o["sorter"].tiles_x, o["sorter"].tiles_y
+            sb = (spread_step_bytes(len(o["rec"]), o["M"], column_items(o["rec"], otx, oty), otx, oty)
+                  if spread_passes(args, otx, oty) else
+                  step_bytes_model(len(o["rec"]), o["M"], otx, oty, o["sorter"].key_bits)[0])
             p50o = pct(o["step_ms"], 50)
             others[wl] = {"num_pairs": o["M"], "num_gaussians": len(o["rec"]), "steps": steps,
                           "pairs_per_s": o["M"] / (o["ms_per_step"] * 1e-3), "ms_per_step": o["ms_per_step"],

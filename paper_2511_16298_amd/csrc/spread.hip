@@ -19,9 +19,9 @@
 // the digits [lo, hi):
 //   1. a bit matrix in LDS, one row of a bit per item for each digit: every
 //      item toggles its bit in the rows where its interval starts and ends,
-//      whatever its length.  The rows are cut into blocks, each walked by the lanes of one row's words;
-//      an item whose interval runs on into a block sets its bit in the
-//      block's opening word.
+//      whatever its length.  The rows are cut into blocks, each walked by
+//      the lanes of one row's words; an item whose interval runs on into a
+//      block sets its bit in the block's opening word.
 //   2. the running XOR down a block's rows, from its opening word, is the
 //      matrix of covered digits.  It is stored back, with the prefix of the
 //      bit counts over a row's 64-bit words; a row's total is the workgroup's
@@ -44,12 +44,11 @@
 //
 // Measured (MI355X, before: expansion into 8-byte items and two digit passes
 // over them, look-back or totals and a ranges kernel beside them): the
-// 6M-Gaussian full-HD frame (11.0M items, 27.6M pairs) 99 + 142 us against
-// 374 us, the frame 589 -> 455 us; the 1M-Gaussian one 29 + 36 against 90,
-// 162.5 -> 144 us; a batch of 64 frames (170M pairs) 638 + 796 against
-// 2,443, 3.41 -> 2.46 ms.  Of a workgroup's 20 us about 5 are its loads, 5 to
-// 8 the look-back and the rest vector and LDS work; the row pass moves
-// 16 B per item and pair at 3.1 TB/s.
+// 6M-Gaussian full-HD frame (11.0M items, 27.6M pairs) 89 + 127 us against
+// 374 us, the frame 589 -> 423 us; the 1M-Gaussian one 26 + 32 against 90,
+// 162.5 -> 132.5 us; a batch of 64 frames (170M pairs) 3.41 -> 2.25 ms.  The
+// row pass moves 16 B per item and pair at 3.5 TB/s; of a workgroup's 20 us
+// about 5 are its loads, 5 the look-back and the rest LDS and vector work.
 #include "common.hpp"
 #include "internal.hpp"
 
