@@ -223,7 +223,7 @@ ss_status ss_count_pairs(const ss_frame* frame, uint32_t* d_tiles_touched, uint3
  * the Gaussians are sorted by depth, their pairs written in depth order and
  * then sorted stably by tile id alone; frames of at most 256 tiles and
  * 16,384 Gaussians (without tiles_touched / offsets outputs) take a
- * two-kernel path; SS_ALGO_DIRECT counts, scans and duplicates in index
+ * one-kernel path; SS_ALGO_DIRECT counts, scans and duplicates in index
  * order and sorts key bits [0, b).  Every path gives the same output. */
 ss_status ss_sort_frame(const ss_frame* frame, const ss_frame_out* out,
                         void* workspace, size_t workspace_bytes, void* stream,
