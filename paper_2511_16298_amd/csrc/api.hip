@@ -1238,6 +1238,7 @@ ss_status ss_render_frame(const ss_frame* frame, const ss_render_desc* desc, voi
     return SS_ERR_INVALID_ARGUMENT;
   RenderArgs a{};
   a.gaussians = frame->gaussians;
+  a.n = frame->num_gaussians;
   a.conic_opacity = desc->conic_opacity;
   a.rgb = desc->rgb;
   a.values = desc->values;

@@ -411,6 +411,7 @@ hipError_t launch_tiny(const TinyArgs& a, hipStream_t s);
 // Render (see render.hip).
 struct RenderArgs {
   const ss_gaussian2d* gaussians;
+  uint32_t n;                   // Gaussians
   const float* conic_opacity;   // [N][4]
   const float* rgb;             // [N][4]
   const uint32_t* values;

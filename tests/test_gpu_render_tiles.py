@@ -51,7 +51,8 @@ def scene(W, H, n, seed, ratio=(0.25, 1.0), opacity=(0.02, 0.99), shrink=(0.3, 1
 
 
 @pytest.mark.parametrize("W,H,n", [(1, 1, 40), (8, 8, 300), (9, 7, 300), (17, 33, 1000), (100, 60, 5000),
-                                   (250, 131, 20_000), (16, 2048, 3000), (640, 360, 50_000)])
+                                   (250, 131, 20_000), (16, 2048, 3000), (640, 360, 50_000),
+                                   (640, 360, 3679), (640, 360, 3680)])
 def test_sizes(W, H, n):
     print(f"{W}x{H} n={n}", flush=True)
     both(W, H, *scene(W, H, n, n + W))
