@@ -487,7 +487,7 @@ __device__ __forceinline__ void store_depth_top(const PassArgs& a, uint32_t* s2)
 
 template <typename K, int RB, int ITEMS, int THREADS, int MODE, bool DROP, bool TIERS>
 __device__ __forceinline__ bool onesweep_body(const PassArgs& a, PassSmem<K, RB, ITEMS, THREADS, MODE>& sm,
-                                              uint32_t t);
+                                              uint32_t t, bool test_status);
 
 // Segmented: publishing workgroup f computes frame f's digit bases for
 // publish_passes passes (from the frame's histograms) and offsets them by the
@@ -633,9 +633,9 @@ constexpr uint32_t tier_blocks() {
 template <typename K, int RB, int ITEMS, int THREADS, int MODE, bool DROP, bool TIERS>
 __global__ __launch_bounds__(THREADS) void k_onesweep(PassArgs a) {
   __shared__ PassSmem<K, RB, ITEMS, THREADS, MODE> sm;
-  if (a.status && *a.status != SS_OK) return;
   constexpr uint32_t kOrder = kTileOrder<ITEMS, THREADS, MODE>;
-  onesweep_body<K, RB, ITEMS, THREADS, MODE, DROP, TIERS>(a, sm, kOrder == 0 ? blockIdx.x : xcd_order<kOrder>(blockIdx.x));
+  onesweep_body<K, RB, ITEMS, THREADS, MODE, DROP, TIERS>(a, sm, kOrder == 0 ? blockIdx.x : xcd_order<kOrder>(blockIdx.x),
+                                                          a.status != nullptr);
   if constexpr (sizeof(K) == 4) {
     if (a.depth_top_out != nullptr && blockIdx.x == 0) store_depth_top<THREADS>(a, sm.dstart);
   }
@@ -643,7 +643,8 @@ __global__ __launch_bounds__(THREADS) void k_onesweep(PassArgs a) {
 
 // A depth pass of the spread path, with side work in the workgroups from
 // side_first on.  Where that sets the status (kTotals), the pass's own
-// workgroups do not read it on entry: they must all run.
+// workgroups do not read it on entry: they must all run (what an earlier pass
+// that gave up left undone they only move, within the arrays).
 template <int ITEMS, int THREADS, bool DROP, bool TIERS>
 __global__ __launch_bounds__(THREADS) void k_depth_side(PassArgs a, SideWork side, uint32_t side_first) {
   __shared__ PassSmem<uint32_t, 8, ITEMS, THREADS, kPassKV> sm;
@@ -656,10 +657,9 @@ __global__ __launch_bounds__(THREADS) void k_depth_side(PassArgs a, SideWork sid
     else side_totals<THREADS>(side, reinterpret_cast<unsigned long long*>(sm.buf), sm.tmp, s_tmp);
     return;
   }
-  if (side.kind != SideWork::kTotals && *a.status != SS_OK) return;
   constexpr uint32_t kOrder = kTileOrder<ITEMS, THREADS, kPassKV>;
   onesweep_body<uint32_t, 8, ITEMS, THREADS, kPassKV, DROP, TIERS>(
-      a, sm, kOrder == 0 ? blockIdx.x : xcd_order<kOrder>(blockIdx.x));
+      a, sm, kOrder == 0 ? blockIdx.x : xcd_order<kOrder>(blockIdx.x), side.kind != SideWork::kTotals);
 }
 
 // Persistent form (64-bit keys, 512 threads, a.tickets): tickets in order
@@ -671,28 +671,32 @@ __global__ __launch_bounds__(THREADS) void k_depth_side(PassArgs a, SideWork sid
 template <typename K, int RB, int ITEMS, int THREADS, int MODE>
 __global__ __launch_bounds__(THREADS, ITEMS >= 16 ? 4 : 6) void k_onesweep_persistent(PassArgs a) {
   __shared__ PassSmem<K, RB, ITEMS, THREADS, MODE> sm;
-  if (a.status && *a.status != SS_OK) return;
   while (true) {
     if (threadIdx.x == 0)
       sm.ticket = a.status && ld_agent(a.status) != SS_OK ? 0xFFFFFFFFu : atomicAdd(a.tickets, 1u);
     __syncthreads();
     const uint32_t t = sm.ticket;
-    if (t == 0xFFFFFFFFu || !onesweep_body<K, RB, ITEMS, THREADS, MODE, false, false>(a, sm, t)) break;
+    if (t == 0xFFFFFFFFu || !onesweep_body<K, RB, ITEMS, THREADS, MODE, false, false>(a, sm, t, false)) break;
     __syncthreads();  // every thread is done with this ticket's LDS
   }
 }
 
 // Workgroup (or ticket) t.  Returns false when t lies past the pass's last
-// tile (a persistent workgroup then stops taking tickets).
+// tile (a persistent workgroup then stops taking tickets).  test_status: leave
+// where the status holds an error.  Another workgroup of the same pass may
+// raise one at any time, so the workgroup goes by one thread's read: were each
+// wave to go by its own, some could leave and the others go on past barriers
+// with parts of the LDS never written.
 template <typename K, int RB, int ITEMS, int THREADS, int MODE, bool DROP, bool TIERS>
 __device__ __forceinline__ bool onesweep_body(const PassArgs& a, PassSmem<K, RB, ITEMS, THREADS, MODE>& sm,
-                                              uint32_t t) {
+                                              uint32_t t, bool test_status) {
   constexpr int TILE = THREADS * ITEMS;
   const uint32_t n = a.num_pairs ? *a.num_pairs : a.n_fixed;
   const int tid = threadIdx.x;
-  if (tid == 0) sm.timeout = 0;
+  if (tid == 0) sm.timeout = test_status && *a.status != SS_OK ? 1u : 0u;
   for (int i = tid; i < (THREADS / kWave) << RB; i += THREADS) sm.wcnt[i] = 0;
   __syncthreads();
+  if (sm.timeout) return false;
   // In a chain's first 64-bit pass workgroup 0 only publishes the digit
   // bases (dispatched first, it has them out before any tile needs them, and
   // no tile's look-back waits on it); tile b is then workgroup b + 1.  A

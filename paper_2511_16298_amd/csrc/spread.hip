@@ -99,7 +99,7 @@ __global__ __launch_bounds__(THREADS, ROWS ? 8 : 6) void k_spread(SpreadArgs a) 
   constexpr uint32_t kPer = S::kPer, kWaves = S::kWaves, kWords = S::kWords, kRowStride = S::kRowStride,
                      kPfxStride = S::kPfxStride, kBlocks = S::kBlocks, kSlots = S::kSlots;
   extern __shared__ __align__(16) unsigned char s_dyn[];
-  __shared__ uint32_t s_timeout;
+  __shared__ uint32_t s_timeout, s_exit[kWaves];
   const Lds<S> at(a.max_digits, ROWS);
   uint64_t* s_bits = reinterpret_cast<uint64_t*>(s_dyn);            // [digits][kRowStride]
   uint16_t* s_pfx = reinterpret_cast<uint16_t*>(s_dyn + at.pfx);    // [digits][kPfxStride]
@@ -114,14 +114,21 @@ __global__ __launch_bounds__(THREADS, ROWS ? 8 : 6) void k_spread(SpreadArgs a) 
   const uint32_t lane = lane_id();
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
 
-  // ---- this workgroup's items (all uniform) ----
+  // ---- this workgroup's items ----
+  // After an error the row pass's chunks are not there, and nothing is read
+  // through one.  But another workgroup of this launch may raise the status
+  // between two waves' reads of it, so a wave that sees an error only takes no
+  // items here; the workgroup leaves as one, after the barrier below.  (The
+  // rest of this part is the same in every wave.)
+  const bool failed = __builtin_amdgcn_readfirstlane(*a.status) != SS_OK;
+  if (lane == 0) s_exit[wave] = failed;
   const SpreadChunk ch = a.chunks[t];
   const uint32_t used = ROWS ? *a.num_chunks : ~0u;
-  if (*a.status != SS_OK || t >= used) return;
-  const uint32_t base = ch.base, n = ch.count & 0xFFFFu, f = ch.frame;
-  const uint32_t col = ch.count >> 16;   // row pass: the column
+  if (t >= used) return;
   // column pass: no live Gaussians here, nor in any later workgroup of the frame
-  if (!ROWS && n == 0) return;
+  if (!ROWS && (ch.count & 0xFFFFu) == 0) return;
+  const uint32_t base = ch.base, n = failed ? 0u : ch.count & 0xFFFFu, f = failed ? 0u : ch.frame;
+  const uint32_t col = ch.count >> 16;   // row pass: the column
 
   // ---- loads: item i = j * THREADS + tid ----
   const FrameInfo& F = a.table[f];
@@ -156,6 +163,7 @@ __global__ __launch_bounds__(THREADS, ROWS ? 8 : 6) void k_spread(SpreadArgs a) 
   for (uint32_t i = tid; i < kBlocks * kRowStride; i += THREADS) s_open[i] = 0;
   if (tid == 0) s_timeout = 0;
   __syncthreads();
+  if (ballot(lane < kWaves && s_exit[lane % kWaves] != 0) != 0) return;
 
   // ---- 1. toggles and opening words ----
   const uint32_t per_block = (digits + kBlocks - 1) / kBlocks;
