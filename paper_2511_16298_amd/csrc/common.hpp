@@ -110,6 +110,13 @@ __device__ __forceinline__ void st_agent(uint64_t* p, uint64_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Raises an error in a status word (SS_OK when the launch began) in which other
+// workgroups may be raising SS_ERR_TIMEOUT at the same time: one that is there
+// already stays, and no SS_OK is ever written over it.
+__device__ __forceinline__ void raise_status(uint32_t* status, uint32_t st) {
+  if (st != SS_OK) atomicCAS(status, static_cast<uint32_t>(SS_OK), st);
+}
+
 // Inclusive scans over the 64 lanes of a wave with DPP lane moves instead of
 // LDS permutes.  Inside each row of 16 lanes, four steps (row_shr:1, 2, 4, 8)
 // add the value d lanes below; lanes below the row's start read 0 (bound_ctrl),

@@ -189,7 +189,7 @@ __global__ __launch_bounds__(kCountThreads) void k_count_dup(CountDupArgs a) {
     else if (DUP && total > a.capacity) st = SS_ERR_CAPACITY;
     *a.num_pairs = total > 0xFFFFFFFFull ? 0xFFFFFFFFu : static_cast<uint32_t>(total);
     // a timeout raised by any workgroup wins over the computed status
-    if (ld_agent(a.status) != SS_ERR_TIMEOUT) *a.status = st;
+    raise_status(a.status, st);
   }
 
   if (a.offsets) {

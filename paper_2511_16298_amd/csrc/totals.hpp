@@ -32,7 +32,7 @@ __device__ __forceinline__ void finish_totals(const PairTotalsArgs& a, unsigned 
     else if (m > 0xFFFFFFFFull) st = SS_ERR_OVERFLOW;
     else if (m > a.capacity) st = SS_ERR_CAPACITY;
     *a.num_pairs = m > 0xFFFFFFFFull ? 0xFFFFFFFFu : static_cast<uint32_t>(m);
-    if (*a.status == SS_OK) *a.status = st;
+    raise_status(a.status, st);
   }
   if (a.frame_pairs == nullptr && a.seg_base == nullptr) return;
   const uint32_t f32 = fm > 0xFFFFFFFFull ? 0xFFFFFFFFu : static_cast<uint32_t>(fm);

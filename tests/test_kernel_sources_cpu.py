@@ -23,3 +23,12 @@ def test_no_wave_leaves_a_pass_by_itself():
     alone = [(at, code.strip()) for at, code in lines("onesweep.hip", "spread.hip")
              if re.search(r"\*\s*a\.status\b.*\breturn\b", code)]
     assert alone == []
+
+
+def test_no_plain_store_to_a_status_others_raise():
+    """Beside workgroups that raise SS_ERR_TIMEOUT, a status computed from the
+    counts is raised atomically: a load and a store could put SS_OK over a
+    timeout.  The small-frame kernel alone has no waits and just stores."""
+    plain = [(at, code.strip()) for at, code in lines()
+             if re.search(r"\*\s*a\.status\s*=[^=]", code) and not at.startswith("tiny.hip:")]
+    assert plain == []
