@@ -135,10 +135,10 @@ typedef struct ss_options {
  * pass); a Gaussian adds at most one pair per tile, so the stable tile sort
  * leaves each tile in (depth, index) order.  radix_bits, items and
  * workgroup_size apply to the passes over the pairs.  At their defaults (8,
- * 16, 512) and with frames of at most 256 tiles per axis, two spread passes
- * take the place of duplication and of the passes over the pairs: one by
- * tile column from the Gaussians, one by tile row from its items.  The
- * result is the same.  AUTO = DEPTH_FIRST,
+ * 16, 512) and where they are the faster way (frames of 8 to 160 tiles per
+ * axis, by and large), two spread passes take the place of duplication and of
+ * the passes over the pairs: one by tile column from the Gaussians, one by
+ * tile row from its items.  The result is the same.  AUTO = DEPTH_FIRST,
  * except that SS_FLAG_UNSORTED implies DIRECT. */
 #define SS_ALGO_AUTO 0u
 #define SS_ALGO_DEPTH_FIRST 1u

@@ -300,57 +300,15 @@ DfLayout make_df_layout(uint32_t n, uint32_t n_frames, uint32_t capacity, uint64
 // depth and span histograms, look-back words; then the plans, the frame
 // table, the Gaussian sort buffers and the column items.
 // ---------------------------------------------------------------------------
-// What the frames of a call have in common for it.
-struct SpreadShape {
-  uint32_t max_tx = 0, max_ty = 0;  // most tile columns and rows of a frame
-  uint64_t sum_tx = 0;              // tile columns of all frames
-  uint64_t col_blocks = 0;          // column-pass workgroups
-  void add(uint32_t n, uint32_t tx, uint32_t ty) {
-    max_tx = tx > max_tx ? tx : max_tx;
-    max_ty = ty > max_ty ? ty : max_ty;
-    sum_tx += tx;
-    col_blocks += (n + kColumnItems - 1) / kColumnItems;
-  }
-};
-
-// Column items per tile column, about: half the pairs, spread over the columns.
-uint64_t mean_column_items(uint32_t capacity, const SpreadShape& sh) {
-  return sh.sum_tx == 0 ? 0 : capacity / 2 / sh.sum_tx;
-}
-
-// Whether a call takes the spread passes: frames of at most 256 tiles per
-// axis (a packed rectangle, and a digit of a pass, hold eight bits), the
-// passes' shape at its default, and a batch that keeps its culled
-// Gaussians (each frame's depth sort then fills its own index range).  The
-// digit passes (depthfirst.hip, onesweep.hip) serve the rest.
+// Whether a call takes the spread passes: where they pay (spread_rule.hpp; at
+// most 256 tiles per axis fit a packed rectangle and a digit), with the passes'
+// shape at its default, and a batch that keeps its culled Gaussians (each
+// frame's depth sort then fills its own index range).  The digit passes
+// (depthfirst.hip, onesweep.hip) serve the rest.
 bool use_spread(uint32_t n, uint32_t n_frames, uint32_t capacity, const SpreadShape& sh, const Options& o) {
-  // a row-pass workgroup per tile column is too many for too few items where
-  // thousands of columns hold under 256 each (64 frames of 5,000 Gaussians:
-  // 127 us in the digit passes, 149 in these; 24 frames of 8,000: 113 and 108)
-  if (sh.sum_tx > 2048 && mean_column_items(capacity, sh) < 256) return false;
-  return n != 0 && o.shape_default && sh.max_tx <= 256 && sh.max_ty <= 256 &&
-         (o.algorithm == SS_ALGO_AUTO || o.algorithm == SS_ALGO_DEPTH_FIRST) &&
+  return o.shape_default && (o.algorithm == SS_ALGO_AUTO || o.algorithm == SS_ALGO_DEPTH_FIRST) &&
          (o.flags & (SS_FLAG_UNSORTED | SS_FLAG_KEY32_LOSSY | SS_FLAG_PERSISTENT)) == 0 &&
-         (n_frames == 1 || (o.flags & SS_FLAG_DROP_CULLED) == 0);
-}
-
-// Items per workgroup of the row pass.  Large ones (4,096 items, 1,024
-// threads) have the fewest workgroups to look back over (6M-Gaussian frame
-// 478 -> 456 us against 2,048, full HD 146 -> 145, 64-frame batch 2.59 ->
-// 2.46 ms), while their LDS lets two share a CU: up to 80 tile rows.  But
-// every tile column has a workgroup of its own, however few its items, so
-// where the columns are more than the GPU holds large workgroups at once
-// (512), their share of the items decides.  Seven frames of 93,000 Gaussians (3,300 items a column) take
-// 134 us with 4,096, 127 with 2,048, 130 with 1,024 items; 39 of 175,000
-// (6,100) 475 / 471 / 487; 46 of 27,000 (950) 250 / 225 / 220; 15 of 18,000
-// (630) 121 / 113 / 107.
-uint32_t row_pass_items(uint32_t capacity, const SpreadShape& sh) {
-  const uint64_t mean = mean_column_items(capacity, sh);
-  if (sh.sum_tx > 512) {
-    if (mean < 1024) return 1024;
-    if (mean < 8192) return 2048;
-  }
-  return sh.max_ty <= 80 ? 4096 : 2048;
+         (n_frames == 1 || (o.flags & SS_FLAG_DROP_CULLED) == 0) && spread_pays(n, n_frames, capacity, sh);
 }
 
 struct SpreadLayout {
@@ -386,7 +344,7 @@ SpreadLayout make_spread_layout(uint32_t n, uint32_t n_frames, uint32_t capacity
   L.col_blocks = static_cast<uint32_t>(sh.col_blocks);
   // column items number at most the pairs; every column may end in a partial
   // workgroup, and one without items still has one
-  L.row_items = row_pass_items(capacity, sh);
+  L.row_items = row_pass_items(n, capacity, sh);
   L.row_blocks = static_cast<uint32_t>((capacity + L.row_items - 1) / L.row_items + sh.sum_tx);
   L.stride_x = (sh.max_tx + 15) / 16 * 16;
   L.stride_y = (sh.max_ty + 15) / 16 * 16;

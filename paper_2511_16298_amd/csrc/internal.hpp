@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "splatsort.h"
+#include "spread_rule.hpp"
 
 namespace ss {
 
@@ -93,9 +94,6 @@ struct PairTotalsArgs {
 constexpr uint32_t kPlanStride = 257;
 constexpr uint32_t kPlanRow = kPlanStride, kPlanChunk = 2 * kPlanStride;
 constexpr uint32_t kPlanWords = 3 * kPlanStride;
-
-// Gaussians per workgroup of the column pass.
-constexpr uint32_t kColumnItems = 2048;
 
 // A workgroup of a spread pass: its items, its frame and the first workgroup
 // of its look-back chain (the frame's first).
