@@ -15,7 +15,7 @@
 // record, 16 waves a CU, then the sort.  Two kernels before it (one bucketing
 // 512 Gaussians per workgroup, on 20 CUs for 10,000, one gathering and sorting
 // the tiles) took 13.8 + 11.5 us for the 256 x 256 frame of 10,000 Gaussians,
-// this one 11.7 (24.4 -> 11.7 us a call).
+// this one 11.4 (24.4 -> 11.4 us a call).
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -98,9 +98,12 @@ __global__ __launch_bounds__(kSortThreads) void k_tiny_frame(TinyArgs a) {
       (static_cast<unsigned long long>(all) << 38) | (static_cast<unsigned long long>(before) << 15) |
           static_cast<uint32_t>(__popc(hits)),
       s_tmp64, sums);
-  const uint32_t n = static_cast<uint32_t>(sums) & 0x7FFFu;
-  const uint32_t start = static_cast<uint32_t>(sums >> 15) & 0x7FFFFFu;
-  const uint32_t m = static_cast<uint32_t>(sums >> 38);
+  // the same in every lane: scalars
+  const uint32_t sums_lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(sums));
+  const uint32_t sums_hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(sums >> 32));
+  const uint32_t n = sums_lo & 0x7FFFu;
+  const uint32_t start = (sums_lo >> 15 | sums_hi << 17) & 0x7FFFFFu;
+  const uint32_t m = sums_hi >> 6;
   uint32_t any_bad = 0;
 #pragma unroll
   for (uint32_t w = 0; w < kSortWaves; ++w) any_bad |= s_bad[w];
@@ -137,14 +140,19 @@ __global__ __launch_bounds__(kSortThreads) void k_tiny_frame(TinyArgs a) {
   const uint64_t tile_hi = static_cast<uint64_t>(t) << 32;
 
   if (n <= kSortThreads) {
-    // items are distinct, so an item's place is the number of smaller ones
-    const uint32_t share = kSortThreads / parts, i = tid % share, part = tid / share, len = n2 / parts;
+    // items are distinct, so an item's place is the number of smaller ones,
+    // read two at a time; a share is whole waves.  Counted in pairs, so that
+    // every read is plainly of 16 aligned bytes, one LDS access each: what this
+    // loop waits for (1,000 items in a tile: 33.6 -> 23.3 us a frame)
+    const uint32_t share = kSortThreads / parts, i = tid % share, len = n2 / (2 * parts);
+    const uint32_t part = __builtin_amdgcn_readfirstlane(tid / share);
+    const ulonglong2* two = reinterpret_cast<const ulonglong2*>(s_buf);
     const uint64_t me = i < n ? s_buf[i] : 0ull;
     uint32_t r = 0;
     if (i < n) {
 #pragma unroll 4
-      for (uint32_t j = part * len; j < (part + 1) * len; j += 2) {
-        const ulonglong2 q = *reinterpret_cast<const ulonglong2*>(s_buf + j);
+      for (uint32_t j = part * len; j < (part + 1) * len; ++j) {
+        const ulonglong2 q = two[j];
         r += (q.x < me) + (q.y < me);
       }
       if (parts != 1 && r != 0) atomicAdd(&s_wcnt[i], r);
