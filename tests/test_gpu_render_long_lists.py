@@ -1,4 +1,5 @@
-"""Lists around the length from which a tile's first batch is half a batch, of
+"""Frames around the number of Gaussians per tile from which the image-only
+kernel is taken, and lists around the length from which a tile's first batch is half a batch, of
 faint entries (the whole list counts) and of opaque ones (the tile ends within
 its first batch, or just past it): the image-only kernel against the counting
 kernel, bit for bit (tolerance 0)."""
@@ -20,3 +21,11 @@ def test_long_lists(n, opacity):
     co[:, 0], co[:, 1], co[:, 2] = 1 / 64.0, 0, 1 / 64.0
     print(f"list of {n}", flush=True)
     both(16, 16, rec, co, cl)
+
+
+@pytest.mark.parametrize("W,H,tiles", [(640, 360, 920), (50, 40, 12), (16, 16, 1)])
+@pytest.mark.parametrize("extra", [-1, 0, 1])
+def test_sparse_frames(W, H, tiles, extra):
+    n = 5 * tiles + extra
+    print(f"{W}x{H} n={n}", flush=True)
+    both(W, H, *scene(W, H, n, n))
