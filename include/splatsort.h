@@ -288,8 +288,9 @@ ss_status ss_batch_count_pairs(const ss_frame* frames, uint32_t n_frames, uint32
  * stream; the workspace must hold ss_plan_workspace_bytes.  Graph capture
  * runs on a stream the plan owns.  With tune_cache (a file path), the choice
  * is looked up first under (device architecture, HIP runtime version, ABI
- * version, and the ceil(log2) of the frame count, Gaussians, pair capacity,
- * total and largest frame's tiles); a hit skips the timing (ss_plan_config
+ * version, revision of the candidates, the ceil(log2) of the frame count,
+ * Gaussians, pair capacity, total and largest frame's tiles, whether the
+ * default shape takes the spread passes, and the options' flags); a hit skips the timing (ss_plan_config
  * then reports no candidate times), a miss times the candidates and records
  * the winner in the file (one text line per key, replaced in place; written
  * through a temporary file and a rename).  A file that cannot be read or

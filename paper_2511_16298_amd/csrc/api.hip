@@ -1173,6 +1173,14 @@ ss_status batch_shape(const ss_frame* frames, uint32_t n_frames, BatchShape* b) 
 }
 
 }  // namespace
+
+bool takes_spread(const ss_frame* frames, uint32_t n_frames, uint32_t capacity, const ss_options& options) {
+  BatchShape b;
+  Options o;
+  if (batch_shape(frames, n_frames, &b) != SS_OK || parse_options(&options, &o) != SS_OK) return false;
+  return make_sort_layout(static_cast<uint32_t>(b.n), n_frames, capacity, b.tiles, o, b.max_n, b.max_tiles, b.spread).spread;
+}
+
 }  // namespace ss
 
 using namespace ss;

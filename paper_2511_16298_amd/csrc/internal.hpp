@@ -105,6 +105,9 @@ struct SpreadChunk {
 };
 static_assert(sizeof(SpreadChunk) == 16, "one 16-byte load");
 
+// Whether ss_sort_batch takes the spread passes for these frames (api.hip).
+bool takes_spread(const ss_frame* frames, uint32_t n_frames, uint32_t capacity, const ss_options& options);
+
 // Work that extra workgroups of the depth passes do beside the pass, so that
 // it costs no launch:
 //   kPlan: one per frame, its plan from the span histograms and its column

@@ -10,6 +10,7 @@
 #include <string>
 #include <vector>
 
+#include "internal.hpp"
 #include "splatsort.h"
 #include "tunecache.hpp"
 
@@ -133,6 +134,9 @@ bool plan_tune_key(const ss_plan* p, hipStream_t s, ss::TuneKey* k) {
   k->pairs_log2 = log2_ceil(p->out.pair_capacity);
   k->tile_bits = log2_ceil(tiles);
   k->frame_tile_bits = log2_ceil(max_tiles);
+  const ss_options o = with(p->options, kCandidates[0]);   // the default shape
+  k->spread = ss::takes_spread(p->frames.data(), static_cast<uint32_t>(p->frames.size()), p->out.pair_capacity, o);
+  k->caller_flags = o.flags;
   return true;
 }
 

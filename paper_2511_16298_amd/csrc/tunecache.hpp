@@ -1,14 +1,16 @@
 // Host-only autotune cache for plans: the pass configuration a plan chose,
-// per device architecture, HIP runtime version, library ABI version and
-// batch size bucket, kept one entry per line in a small text file so that
+// per device architecture, HIP runtime version, library ABI version, revision
+// of the candidates, batch size bucket and what else decides which kernels a
+// configuration runs, kept one entry per line in a small text file so that
 // later plans of the same shape skip the timing.  Free of HIP, so that it
 // can be built and tested on its own (with sanitizers) on any host.
 //
 // Line format (fields separated by single spaces):
 //   ss-tune 1 <arch> <runtime> <abi> <frames_log2> <gaussians_log2>
-//             <pairs_log2> <tile_bits> <frame_tile_bits> = <radix_bits>
-//             <items> <threads> <flags> <ms>
-// Lines that do not parse are ignored by lookups and kept by updates.
+//             <pairs_log2> <tile_bits> <frame_tile_bits> <revision> <spread>
+//             <caller_flags> = <radix_bits> <items> <threads> <flags> <ms>
+// Lines that do not parse are ignored by lookups and kept by updates; so are
+// lines of earlier revisions (the first had no fields after frame_tile_bits).
 #pragma once
 
 #include <stdint.h>
@@ -19,16 +21,23 @@
 
 namespace ss {
 
+// Raised whenever a candidate comes to run other kernels, or kernels of other
+// speed, so that choices timed before are timed again.  2: the default shape
+// takes the spread passes where they pay.
+constexpr uint32_t kTuneRevision = 2;
+
 struct TuneKey {
   std::string arch;          // device architecture name (no spaces; see tune_arch_token)
   int32_t runtime = 0;       // HIP runtime version
   uint32_t abi = 0;          // library ABI version
   uint32_t frames_log2 = 0, gaussians_log2 = 0, pairs_log2 = 0, tile_bits = 0, frame_tile_bits = 0;
+  uint32_t spread = 0;       // 1: the default shape takes the spread passes for these frames
+  uint32_t caller_flags = 0; // the plan's SS_FLAG_* that every candidate keeps
 
   std::string str() const {
-    char buf[160];
-    snprintf(buf, sizeof(buf), "%d %u %u %u %u %u %u", runtime, abi, frames_log2, gaussians_log2, pairs_log2,
-             tile_bits, frame_tile_bits);
+    char buf[192];
+    snprintf(buf, sizeof(buf), "%d %u %u %u %u %u %u %u %u %u", runtime, abi, frames_log2, gaussians_log2, pairs_log2,
+             tile_bits, frame_tile_bits, kTuneRevision, spread, caller_flags);
     return "ss-tune 1 " + arch + " " + buf;
   }
 };
