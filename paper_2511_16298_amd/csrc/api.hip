@@ -1101,17 +1101,6 @@ bool tiny_shape(uint32_t n, uint32_t num_tiles, const Options& o) {
          n <= kTinyMaxGaussians;
 }
 
-// The workspace asked for on this path: room for the pairs of every 512
-// Gaussians grouped by tile, with counts and prefixes.  The kernel does
-// without, but what callers are asked for stays as it was published.
-size_t tiny_workspace(uint32_t n, uint32_t num_tiles, uint32_t capacity) {
-  const uint32_t groups = (n + 511) / 512;
-  const uint64_t most = static_cast<uint64_t>(512) * num_tiles;
-  const uint64_t region = most < capacity ? most : capacity;
-  return align_up(align_up(static_cast<size_t>(groups) * (2 * num_tiles + 1) * sizeof(uint32_t)) +
-                  static_cast<size_t>(groups) * region * sizeof(uint64_t));
-}
-
 ss_status run_tiny(Launcher& L, const ss_frame* frame, const Geometry& g, const ss_frame_out* out, hipStream_t s) {
   TinyArgs a{};
   a.gaussians = frame->gaussians;
@@ -1293,16 +1282,10 @@ ss_status ss_workspace_bytes(const ss_frame* frame, uint32_t pair_capacity, cons
   Options o;
   SS_TRY(parse_options(options, &o));
   if (pair_capacity > SS_MAX_PAIR_CAPACITY) return SS_ERR_INVALID_ARGUMENT;
-  size_t sort = use_direct(o) ? make_layout(frame->num_gaussians, pair_capacity, g.key_bits, o).total
-                              : make_df_layout(frame->num_gaussians, 1, pair_capacity, g.num_tiles, o,
-                                               frame->num_gaussians, g.num_tiles).total;
-  // small frames take the one-kernel path unless per-Gaussian outputs are
-  // asked for, so both layouts must fit (the extra 8 words hold the status
-  // when the caller gives none)
-  if (tiny_shape(frame->num_gaussians, g.num_tiles, o)) {
-    const size_t tiny = tiny_workspace(frame->num_gaussians, g.num_tiles, pair_capacity) + 256;
-    sort = sort > tiny ? sort : tiny;
-  }
+  const size_t sort = use_direct(o) ? make_layout(frame->num_gaussians, pair_capacity, g.key_bits, o).total
+                                    : make_df_layout(frame->num_gaussians, 1, pair_capacity, g.num_tiles, o,
+                                                     frame->num_gaussians, g.num_tiles).total;
+  // (small frames mostly take the one-kernel path, which needs two words of it)
   // ss_count_pairs runs in any workspace sized here (its own layout can be
   // the larger one, e.g. for N = 0)
   const size_t count = make_layout(frame->num_gaussians, 0, g.key_bits, Options{}).total;
@@ -1358,10 +1341,10 @@ ss_status ss_sort_frame(const ss_frame* frame, const ss_frame_out* out, void* wo
   Launcher L(s, o.timer);
   if (use_direct(o)) return run_direct(L, frame, g, out, o, workspace, s);
   if (tiny_shape(frame->num_gaussians, g.num_tiles, o) && out->tiles_touched == nullptr && out->offsets == nullptr) {
-    // status and pair count: the caller's words, else the workspace's last 256 bytes
+    // status and pair count: the caller's words, else the workspace's first
     ss_frame_out o2 = *out;
-    if (o2.status == nullptr) o2.status = at<uint32_t>(workspace, need - 256);
-    if (o2.num_pairs == nullptr) o2.num_pairs = at<uint32_t>(workspace, need - 256) + 1;
+    if (o2.status == nullptr) o2.status = at<uint32_t>(workspace, 0);
+    if (o2.num_pairs == nullptr) o2.num_pairs = at<uint32_t>(workspace, 0) + 1;
     return run_tiny(L, frame, g, &o2, s);
   }
   const FrameInfo fi = frame_info(frame, g, 0, 0);

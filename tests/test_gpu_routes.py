@@ -207,3 +207,23 @@ def test_spread_uneven_batch(wide):
     assert np.array_equal(u32(s.tile_ranges).reshape(-1, 2), o.ranges)
     assert np.array_equal(u32(s.frame_pairs), o.num_pairs.astype(np.uint32))
     assert np.array_equal(u32(s.frame_pair_base), o.pair_base.astype(np.uint32))
+
+
+# ------------------------------------------------------------- small frames
+
+@pytest.mark.parametrize("n", [0, 1, 3000, 16_384])
+def test_small_frames_without_status_and_count(n):
+    """Without the caller's words for them, the status and the pair count lie
+    in the workspace's first two; an exact workspace serves."""
+    rec = synth.make_frame(synth.FrameSpec(256, 256, max(n, 1)), 9900)[:n]
+    o = oracle.sort_frame(256, 256, rec, stages=False)
+    s = ss.FrameSorter(256, 256, n, o.num_pairs)
+    s._cout.status = s._cout.num_pairs = None
+    s.workspace = torch.full((s.workspace_bytes + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    assert route(s, ss.records_to_device(rec)) == "small"
+    words = s.workspace[:8].cpu().numpy().view(np.uint32)
+    assert words[0] == 0 and words[1] == o.num_pairs
+    assert bool((s.workspace[s.workspace_bytes:] == 0x5A).all().item())
+    assert np.array_equal(u64(s.out.keys)[:o.num_pairs], o.keys)
+    assert np.array_equal(u32(s.out.values)[:o.num_pairs], o.values)
+    assert np.array_equal(u32(s.out.tile_ranges).reshape(-1, 2), o.ranges)
