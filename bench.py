@@ -39,8 +39,9 @@ import synth  # noqa: E402
 
 PEAK_HBM_GBS = 8000.0   # MI355X HBM3E, published
 DEFAULT_WORKLOAD = "large-6m"
-PASS_SOURCE = os.path.join(ROOT, "paper_2511_16298_amd", "csrc", "spread.hip")
-API_SOURCE = os.path.join(ROOT, "paper_2511_16298_amd", "csrc", "api.hip")
+STEP_SOURCES = tuple(os.path.join(ROOT, "paper_2511_16298_amd", "csrc", f) for f in (
+    "spread.hip", "spread_rule.hpp", "onesweep.hip", "depthfirst.hip", "frame_kernels.hip", "totals.hpp", "common.hpp",
+    "internal.hpp", "api.hip"))
 PROFILES = os.path.join(ROOT, "profiles")
 PASS_KERNEL = "k_spread"
 
@@ -88,10 +89,11 @@ def parse():
 
 
 def source_hash(paths=None) -> str:
-    """sha256[:16] of the sources that decide a profiled kernel: the sort pass
-    kernel together with the host code that picks its launch shapes."""
+    """sha256[:16] of the sources that decide a profile: by default those of
+    every kernel of a frame's step (its traffic and time are recorded whole)
+    and the host code that picks its launch shapes."""
     if paths is None:
-        paths = (PASS_SOURCE, API_SOURCE)
+        paths = STEP_SOURCES
     if isinstance(paths, str):
         paths = (paths,)
     h = hashlib.sha256()
@@ -108,7 +110,7 @@ def dominant_kernel(workload: str):
         return "k_preprocess", "", os.path.join(ROOT, "paper_2511_16298_amd", "csrc", "preprocess.hip")
     if workload == "render":
         return "k_render", "", os.path.join(ROOT, "paper_2511_16298_amd", "csrc", "render.hip")
-    return PASS_KERNEL, "<true", (PASS_SOURCE, API_SOURCE)
+    return PASS_KERNEL, "<true", STEP_SOURCES
 
 
 def _rows(pattern: str):
@@ -127,7 +129,7 @@ def summarize_profiles(d: str, workload: str, copy_mib: int = 512,
     lines = [f"# rocprofv3 kernel statistics, workload {workload}",
              "command: rocprofv3 --kernel-trace --stats --output-format csv -d DIR/stats -o run -- "
              f"python3 bench.py --workload {workload} {profiled_args}",
-             f"{dominant_kernel(workload)[0]} sources (kernel, launch shapes) sha256[:16]: {source_hash(dominant_kernel(workload)[2])}", "",
+             f"{dominant_kernel(workload)[0]} sources (kernels, launch shapes) sha256[:16]: {source_hash(dominant_kernel(workload)[2])}", "",
              "| kernel | calls | avg us | min us | max us | share % |", "|---|---|---|---|---|---|"]
     for r in stats:
         name = r["Name"]
@@ -793,10 +795,10 @@ def column_items(rec, tiles_x: int, tiles_y: int) -> int:
 
 
 def spread_passes(args, tiles_x: int, tiles_y: int) -> bool:
-    """Whether the benchmark's arguments take the column and row passes (the
-    default shape, at most 256 tiles per axis)."""
+    """Whether the benchmark's arguments take the column and row passes on one
+    of its frames (the default shape, axes of 8 to 160 tiles)."""
     return (args.algorithm == "depth-first" and args.radix_bits in (0, 8) and args.items in (0, 16)
-            and args.wg in (0, 512) and tiles_x <= 256 and tiles_y <= 256)
+            and args.wg in (0, 512) and 8 <= min(tiles_x, tiles_y) and max(tiles_x, tiles_y) <= 160)
 
 
 def spread_step_bytes(n: int, m: int, c: int, tiles_x: int, tiles_y: int) -> float:

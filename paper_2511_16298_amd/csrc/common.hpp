@@ -24,11 +24,13 @@ constexpr uint64_t kLbMask64 = (1ull << 61) - 1;
 // A published digit base (counts stay below 2^30).
 constexpr uint32_t kBasePublished = 1u << 31;
 
-// Look-back order.  Workgroup b takes tile b of the input and waits only on
-// workgroups with smaller indices.  The dispatcher hands each XCD its
+// Look-back order.  Workgroup b takes tile b of the input, or, in the passes
+// that order tiles by XCD (xcd_order below), a tile of the same group of 64,
+// and waits only on smaller tiles.  The dispatcher hands each XCD its
 // workgroups in increasing index order, so the smallest undispatched
-// workgroup always finds a slot once the running, smaller ones finish: no
-// wait can block forever, and no atomic ticket (whose same-address atomics
+// workgroup always finds a slot once the running, smaller ones finish, and a
+// whole group is in flight long before the GPU is full: no wait can block
+// forever, and no atomic ticket (whose same-address atomics
 // serialise at about 12 ns per workgroup) is needed.  Results do not depend
 // on the dispatch order at all; the bounded spin below only guards progress.
 //

@@ -5,13 +5,15 @@
 // k_render_tiles, the one a caller gets for the image alone with the usual
 // thresholds (described there);
 // k_render, for exact compositing and for the statistics, which evaluate
-// every list entry at every pixel, and for the image of a frame with fewer than
-// five Gaussians per tile, whose lists are so short that a quarter of the
-// workgroups counts for more (full HD, k_render / k_render_tiles, us: splats of
-// 1-12 px, 4 a tile 22.3 / 23.4, 5 a tile 24.8 / 24.6, 6 a tile 27.8 / 25.8; of
-// 1-3 px, 4 a tile 15.1 / 18.7, 8 a tile 20.5 / 20.4; of 8-24 px, 4 a tile 42.7
-// / 38.5; 640 x 360, 1-12 px, 4 a tile 9.4 / 9.1.  The lists are known on the
-// GPU only, so the line lies where middling splats break even): one wave64 owns one tile, lane l holds the four pixels l,
+// every list entry at every pixel, and for the image of a frame with fewer
+// than five Gaussians per tile, whose lists are so short that a quarter of the
+// workgroups counts for more.  (Full HD, k_render / k_render_tiles, us: splats
+// of 1-12 px, 4 a tile 22.3 / 23.4, 5 a tile 24.8 / 24.6, 6 a tile 27.8 /
+// 25.8; of 1-3 px, 4 a tile 15.1 / 18.7, 8 a tile 20.5 / 20.4; of 8-24 px, 4 a
+// tile 42.7 / 38.5; 640 x 360, 1-12 px, 4 a tile 9.4 / 9.1.  The lists are
+// known on the GPU only, so the line lies where middling splats break even.)
+//
+// In k_render one wave64 owns one tile, lane l holds the four pixels l,
 // l + 64, l + 128, l + 192 of the tile (rows l/16, l/16 + 4, ...).
 // Every 64 list entries the lanes load one Gaussian each (mean, conic and
 // opacity, colour) and store its nine per-Gaussian values in the wave's own
