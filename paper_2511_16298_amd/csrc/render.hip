@@ -6,12 +6,13 @@
 // thresholds (described there);
 // k_render, for exact compositing and for the statistics, which evaluate
 // every list entry at every pixel, and for the image of a frame with fewer
-// than five Gaussians per tile, whose lists are so short that a quarter of the
-// workgroups counts for more.  (Full HD, k_render / k_render_tiles, us: splats
-// of 1-12 px, 4 a tile 22.3 / 23.4, 5 a tile 24.8 / 24.6, 6 a tile 27.8 /
-// 25.8; of 1-3 px, 4 a tile 15.1 / 18.7, 8 a tile 20.5 / 20.4; of 8-24 px, 4 a
-// tile 42.7 / 38.5; 640 x 360, 1-12 px, 4 a tile 9.4 / 9.1.  The lists are
-// known on the GPU only, so the line lies where middling splats break even.)
+// than four Gaussians per tile, whose lists are so short that a quarter of the
+// workgroups counts for more (0.4 a tile at full HD: 10.2 against 15.8 us; 1.5
+// a tile at 1264 x 832: 9.8 / 10.9; 2.3 at full HD: 18.7 / 19.8).  With four a
+// tile and footprints of the usual kinds, k_render / k_render_tiles take 26.0 /
+// 21.6 us at full HD, 17.4 / 13.5 at 1264 x 832, 10.6 / 9.9 at 640 x 360.  The
+// lists are known on the GPU only: frames of nothing but round splats of 1-3 px
+// would break even at eight a tile (four: 15.1 / 18.7, six: 17.7 / 19.1).
 //
 // In k_render one wave64 owns one tile, lane l holds the four pixels l,
 // l + 64, l + 128, l + 192 of the tile (rows l/16, l/16 + 4, ...).
@@ -352,6 +353,7 @@ __global__ __launch_bounds__(kTileThreads) void k_render_tiles(RenderArgs a) {
         live = ballot(T > 0.0f) != 0;
       }
     }
+    if (end - b <= count) break;   // the last batch
     // every wave is done with the slots; the tile ends when all its pixels have
     if (!__syncthreads_or(live)) break;
     if (b == start && next < end) load(next);
@@ -378,7 +380,7 @@ hipError_t launch_render(const RenderArgs& a, bool exact, hipStream_t s) {
   if (exact && stats) hipLaunchKernelGGL((k_render<true, true>), g, t, 0, s, a);
   else if (exact) hipLaunchKernelGGL((k_render<true, false>), g, t, 0, s, a);
   else if (stats) hipLaunchKernelGGL((k_render<false, true>), g, t, 0, s, a);
-  else if (a.n < 5ull * tiles) hipLaunchKernelGGL((k_render<false, false>), g, t, 0, s, a);
+  else if (a.n < 4ull * tiles) hipLaunchKernelGGL((k_render<false, false>), g, t, 0, s, a);
   else hipLaunchKernelGGL(k_render_tiles, dim3(xcd_grid<kTileRun>(tiles)), dim3(kTileThreads), 0, s, a);
   return hipGetLastError();
 }

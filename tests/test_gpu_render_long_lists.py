@@ -26,6 +26,6 @@ def test_long_lists(n, opacity):
 @pytest.mark.parametrize("W,H,tiles", [(640, 360, 920), (50, 40, 12), (16, 16, 1)])
 @pytest.mark.parametrize("extra", [-1, 0, 1])
 def test_sparse_frames(W, H, tiles, extra):
-    n = 5 * tiles + extra
+    n = 4 * tiles + extra
     print(f"{W}x{H} n={n}", flush=True)
     both(W, H, *scene(W, H, n, n))
